@@ -155,6 +155,20 @@ struct EpiResidual {
   float* H;
   const float* bias;
   int ldh, M, N;
+  // K split over ns workgroups per tile: split 0 adds its sum (and the bias)
+  // to H, split s > 0 stores its sum to part + (s - 1) * M * ldh, which the
+  // reader of H adds.
+  float* part = nullptr;
+  int ns = 1;
+  bool add = true;  // this workgroup's split is 0
+  __device__ __forceinline__ int splits() const { return ns; }
+  __device__ __forceinline__ void select(int split) {
+    if (split > 0) {
+      H = part + (size_t)(split - 1) * M * ldh;
+      bias = nullptr;
+      add = false;
+    }
+  }
   __device__ __forceinline__ const float* park_bias() const { return bias; }
   // One buffer resource over the wave's rows from r0 (rows past M read as
   // zero, stores to them are dropped), one lane offset; rows step by a scalar
@@ -162,14 +176,15 @@ struct EpiResidual {
   // through readfirstlane: the clamp compiles to a vector med3, and a
   // descriptor word in a VGPR would make every access a per-lane (waterfall)
   // loop.
-  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_from(int r0, int nrows) const {
-    const int rows = __builtin_amdgcn_readfirstlane(min(max(M - r0, 0), nrows));
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_from(int r0, int nrows, bool any = true) const {
+    const int rows = __builtin_amdgcn_readfirstlane(any ? min(max(M - r0, 0), nrows) : 0);
     return __builtin_amdgcn_make_buffer_rsrc((void*)(H + (size_t)min(r0, M) * ldh), (short)0, rows * ldh * 4,
                                              0x00020000);
   }
   template <int TM, int TN>
   __device__ void load_acc(f32x16 (&hv)[TM][TN], int r0, int c0, int lane) const {
-    const __amdgpu_buffer_rsrc_t rh = rows_from(r0, TM * 32);
+    // a split without the residual reads zeros: a resource of no rows
+    const __amdgpu_buffer_rsrc_t rh = rows_from(r0, TM * 32, add);
     const int voff = (((lane >> 5) * 4) * ldh + c0 + (lane & 31)) * 4;
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
@@ -383,7 +398,7 @@ __device__ __forceinline__ void buffer_load_lds16(__amdgpu_buffer_rsrc_t r, void
 // [0, Kw) and [Kw, 2 Kw) multiply the same W, so an operand carried as
 // a hi + lo pair of bf16 values side by side ([M][2 Kw]) yields
 // hi * W^T + lo * W^T in one accumulator.
-template <int BM, int BN, int WM, int WN, int NW, bool WT, class Epi, int WS = 2>
+template <int BM, int BN, int WM, int WN, int NW, bool WT, class Epi, int WS = 2, int AS = 2>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __restrict__ A, int lda, WOperand W,
                                                                 int M, int N, int K, int Kw, Epi epi) {
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -394,11 +409,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
   static_assert(A_INST >= 1 && B_INST >= 1, "tile too small for the wave count");
   // WS = 2: two slabs of A and W side by side; WS = 3: two A slots, then
   // three W slots, so that W runs two slabs ahead
-  static_assert(WS == 2 || WS == 3, "two or three weight slots");
-  __shared__ __attribute__((aligned(1024))) char smem[(2 * BM + WS * BN) * ROWB];
+  static_assert(AS == 2 ? (WS == 2 || WS == 3) : (AS == WS && AS > 2), "two or three weight slots, or a ring of both");
+  __shared__ __attribute__((aligned(1024))) char smem[(AS * BM + WS * BN) * ROWB];
   auto a_slot = [&](int i) -> char* { return WS == 2 ? smem + i * (BM + BN) * ROWB : smem + i * BM * ROWB; };
   auto w_slot = [&](int i) -> char* {
-    return WS == 2 ? smem + i * (BM + BN) * ROWB + BM * ROWB : smem + (2 * BM + i * BN) * ROWB;
+    return WS == 2 ? smem + i * (BM + BN) * ROWB + BM * ROWB : smem + (AS * BM + i * BN) * ROWB;
   };
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -414,6 +429,19 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
   const int nwg = gridDim.x;
   int id = blockIdx.x;
   if ((nwg & 7) == 0) id = (id & 7) * (nwg >> 3) + (id >> 3);
+  // this workgroup's k slabs [kt0, kt0 + nk)
+  int kt0 = 0, nk = K / BK;
+  if constexpr (Epi::kDirect) {
+    const int ns = epi.splits();
+    if (ns > 1) {
+      const int tiles = nwg / ns, split = id / tiles;
+      id -= split * tiles;
+      epi.select(split);
+      const int all = nk;
+      kt0 = split * all / ns;
+      nk = (split + 1) * all / ns - kt0;
+    }
+  }
   const int group = GROUP_M * tiles_n;
   const int first_m = (id / group) * GROUP_M;
   const int gsz = min(tiles_m - first_m, GROUP_M);
@@ -476,10 +504,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
   const int a_row0 = (wm * WM + fi) * ROWB, b_row0 = (wn * WN + fi) * ROWB;
   const int key = (fi >> 1) & 7;
   bf16x8 fa[2][TM], fb[2][TN];
-  // fragments of k16 step ks of slab s (buffer s & 1) into register slot `slot`
-  // (W slab s lies in W slot ws: s & 1 for two slots, s % 3 for three)
-  auto frags = [&](int s, int ws, int ks, int slot) {
-    const char* abase = a_slot(s & 1);
+  // fragments of k16 step ks of the slab in A slot `as` and W slot `ws` into register slot `slot`
+  auto frags = [&](int as, int ws, int ks, int slot) {
+    const char* abase = a_slot(as);
     const char* wbase = w_slot(ws);
     const int off = (((2 * ks + fh) ^ key) << 4);
 #pragma unroll
@@ -492,7 +519,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
   // the 256-thread group (0 in a 4-wave workgroup)
   const int grp = NW > 4 ? tid >> 8 : 0, t = tid & 255;
 
-  const int nk = K / BK;
   // the MFMAs of one k16 step from fragment slot `cur`
   auto step = [&](int cur) {
     __builtin_amdgcn_sched_barrier(0);
@@ -507,42 +533,70 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
   // step already loaded), each reading the next step's fragments before its
   // MFMAs (left alone, the scheduler sinks each read onto its first use)
   constexpr int KS = BK / 16, LAST = (KS - 1) & 1;
-  auto head = [&](int kt, int ws) {
+  auto head = [&](int as, int ws) {
 #pragma unroll
     for (int ks = 0; ks + 1 < KS; ++ks) {
-      frags(kt, ws, ks + 1, (ks & 1) ^ 1);
+      frags(as, ws, ks + 1, (ks & 1) ^ 1);
       step(ks & 1);
     }
   };
-  auto slab = [&](int kt, int ws) {
-    head(kt, ws);
+  auto slab = [&](int as, int ws) {
+    head(as, ws);
     step(LAST);
   };
-  int wl = 0;  // W slot of the last slab
+  int wl = 0, al = 0;  // slots of the last slab
   if constexpr (WS == 2) {
-    issue(0, 0);
+    issue(kt0 * BK, 0);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     frags(0, 0, 0, 0);
     for (int kt = 0; kt + 1 < nk; ++kt) {
       // the other buffer was last read before the previous slab's barrier
-      issue((kt + 1) * BK, (kt + 1) & 1);
-      slab(kt, kt & 1);
+      issue((kt0 + kt + 1) * BK, (kt + 1) & 1);
+      slab(kt & 1, kt & 1);
       // the next slab's loads; this wave's fragment reads are consumed
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
-      frags(kt + 1, (kt + 1) & 1, 0, 0);
+      frags((kt + 1) & 1, (kt + 1) & 1, 0, 0);
     }
-    wl = (nk - 1) & 1;
+    wl = al = (nk - 1) & 1;
+  } else if constexpr (AS > 2) {
+    // a ring of AS slabs, AS - 1 of them ahead of the one being multiplied;
+    // past the last slab the issue repeats it into a free slot (in bounds,
+    // never read), so that every wait counts the same loads.  Each slab's
+    // last k16 step runs after the slab barrier, as below.
+    constexpr int PER = A_INST + B_INST, LEFT = (AS - 2) * PER;
+    static_assert(LEFT < 64, "vmcnt range");
+#pragma unroll
+    for (int i = 0; i < AS - 1; ++i) issue((kt0 + min(i, nk - 1)) * BK, i);
+    __builtin_amdgcn_s_waitcnt((LEFT & 15) | ((LEFT >> 4) << 14) | 0x0070);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    frags(0, 0, 0, 0);
+    int cs = 0, is = AS - 1;  // slot of slab kt, slot of slab kt - 1
+    for (int kt = 0; kt + 1 < nk; ++kt) {
+      // slab kt - 1 was last read before the previous barrier
+      issue((kt0 + min(kt + AS - 1, nk - 1)) * BK, is);
+      head(cs, cs);
+      // slab kt + 1 landed; every wave's reads of slab kt are done
+      __builtin_amdgcn_s_waitcnt((LEFT & 15) | ((LEFT >> 4) << 14) | 0x0070);
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      is = cs;
+      cs = cs == AS - 1 ? 0 : cs + 1;
+      frags(cs, cs, 0, 0);
+      step(LAST);
+    }
+    wl = al = cs;
   } else {
     // W slabs 0 and 1 ahead of A slab 0; past the last slab, W loads repeat
     // the last one (in bounds, into a free slot, never read).  The last k16
     // step of each slab runs after the slab barrier, from fragments read
     // before it, and so covers the latency of the next slab's first
     // fragment reads.
-    issue_a(0, 0);
-    issue_w(0, 0);
-    issue_w(min(1, nk - 1) * BK, 1);
+    issue_a(kt0 * BK, 0);
+    issue_w(kt0 * BK, 0);
+    issue_w((kt0 + min(1, nk - 1)) * BK, 1);
     __builtin_amdgcn_s_waitcnt((B_INST & 15) | ((B_INST >> 4) << 14) | 0x0070);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -552,19 +606,20 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
       // A slot (kt+1)&1 and W slot (kt+2)%3 (slab kt-1) were last read
       // before the previous barrier
       const int wn2 = ws == 0 ? 2 : ws - 1;
-      issue_a((kt + 1) * BK, (kt + 1) & 1);
-      issue_w(min(kt + 2, nk - 1) * BK, wn2);
-      head(kt, ws);
+      issue_a((kt0 + kt + 1) * BK, (kt + 1) & 1);
+      issue_w((kt0 + min(kt + 2, nk - 1)) * BK, wn2);
+      head(kt & 1, ws);
       // A(kt+1) and W(kt+1) landed; W(kt+2) may stay in flight across the
       // barrier; every wave's reads of slab kt are done
       __builtin_amdgcn_s_waitcnt((B_INST & 15) | ((B_INST >> 4) << 14) | 0x0070);
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       ws = ws == 2 ? 0 : ws + 1;
-      frags(kt + 1, ws, 0, 0);
+      frags((kt + 1) & 1, ws, 0, 0);
       step(LAST);  // slab kt's last step
     }
     wl = ws;
+    al = (nk - 1) & 1;
   }
   // the last slab, peeled so that loads issued behind it are straight-line
   // code the compiler's wait counting can follow
@@ -582,7 +637,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
       pb[tn] = (bias && col < N) ? bias[col] : 0.f;
     }
   }
-  slab(nk - 1, wl);
+  slab(al, wl);
   __builtin_amdgcn_s_waitcnt(0);
   if constexpr (Epi::kViaLds) {
     if (bias) {
@@ -650,11 +705,74 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
   }
 }
 
+// ------------------------------------------------------------ choice of tile
+//
+// A product's tile, and for a residual product the number of K splits, is the
+// one whose estimated time is least.  The estimate: a workgroup spends t us on
+// each of its 64-k slabs and f us on its prologue and epilogue; workgroups run
+// in rounds of 256 (one per CU) or 512 (two per CU), and t grows with the
+// number that run together, since they share L2 and HBM: t0 for few, t1 for
+// one on every CU, t2 for two.  The figures are a least-squares fit to 700
+// timings over M = 19..6144 of the 7B, 0.5B and ViT-L products with their
+// weights read from HBM (mean error 6-11%).  What the choice gives against one
+// rule on the tile count (64x128 two-slot tiles up to half a round of
+// 128x128, those up to 512 tiles of 256x256), us:
+//   O-projection M=203 50.7 -> 20, M=1001 55.3 -> 38.6, M=2048 71.7 -> 67
+//   down         M=203 127  -> 34 (with the reduction), M=2048 185 -> 161
+//   7B QKV       M=203 57   -> 38, gate/up M=512 131 -> 90, M=1024 203 -> 171
+// Few workgroups leave each CU waiting on the latency of its own slab loads,
+// so the small tiles keep a ring of 3-4 slabs of both operands; large grids
+// are bound by L2 -> LDS traffic and want the large tiles.
+enum TileId {
+  T_64x64, T_64x128, T_128x128, T_128x128_PAIR, T_256x128, T_256x256, T_256x192, T_192x384, T_192x256, T_COUNT
+};
+struct TileCost {
+  int bm, bn, per_cu;
+  bool whole_n;  // only for N a multiple of bn
+  float t0, t1, t2, f;
+};
+constexpr TileCost kTiles[T_COUNT] = {
+    {64, 64, 2, false, 0.25f, 0.30f, 0.44f, 2.5f},     // 64 KB of LDS
+    {64, 128, 2, false, 0.38f, 0.46f, 0.82f, 3.5f},    // 72 KB
+    {128, 128, 1, false, 0.38f, 0.55f, 0.f, 5.f},      // 128 KB, 8 waves
+    {128, 128, 2, false, 0.54f, 0.65f, 1.0f, 5.5f},    // 80 KB, 4 waves
+    {256, 128, 1, false, 0.55f, 0.89f, 0.f, 7.f},      // 144 KB
+    {256, 256, 1, false, 1.07f, 1.31f, 0.f, 10.f},     // 160 KB
+    {256, 192, 1, true, 1.05f, 1.28f, 0.f, 10.f},      // 136 KB (QKV)
+    {192, 384, 1, true, 1.4f, 1.8f, 0.f, 20.f},        // 144 KB (QKV)
+    {192, 256, 1, true, 0.9f, 1.15f, 0.f, 11.f},       // 144 KB (GELU)
+};
+// Estimated us of an M x N product over nk slabs, K split ns ways.  A split
+// writes and reads ns - 1 fp32 partials and rewrites the sum (4 TB/s), and
+// adds 2 us to the reader.
+inline float tile_us(const TileCost& c, int M, int N, int nk, int ns) {
+  const long w = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * ns;
+  const long slots = 256L * c.per_cu, full = w / slots, rem = w % slots;
+  auto round_t = [&](long x) {
+    return x <= 256 ? c.t0 + (c.t1 - c.t0) * (float)x / 256.f : c.t1 + (c.t2 - c.t1) * (float)(x - 256) / 256.f;
+  };
+  const float slabs = (float)nk / (float)ns;
+  float us = (float)full * (round_t(slots) * slabs + c.f);
+  if (rem) us += round_t(rem) * slabs + c.f;
+  if (ns > 1) us += 2.f + (float)M * (float)N * (8.f * (ns - 1) + 4.f) / 4.0e6f;
+  return us;
+}
+template <class Epi>
+constexpr bool tile_allowed(int id) {
+  constexpr bool qkv = std::is_same<Epi, EpiQKV>::value, gelu = std::is_same<Epi, EpiGelu>::value;
+  return id == T_64x64 ? !Epi::kActInRegs  // SwiGLU needs 64-column waves
+         : id == T_256x256 ? Epi::kBig
+         : id == T_256x192 || id == T_192x384 ? qkv
+         : id == T_192x256 ? gelu
+                           : true;
+}
+
 // A [M][a_parts * K]: a_parts column blocks of K, each multiplied by the
 // same W [N][K] into one accumulator (2: a hi + lo operand pair).
 template <bool WT, class Epi>
 hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int K, const Epi& epi, hipStream_t s,
-                  int a_parts = 1) {
+                  int a_parts = 1, int max_parts = 0, int* parts_used = nullptr) {
+  if (parts_used) *parts_used = 0;
   if (M <= 0 || N <= 0) return hipSuccess;
   if (K % BK != 0 || lda % 8 != 0 || a_parts < 1 || a_parts > 2 || lda < a_parts * K) return hipErrorInvalidValue;
   if (WT) {
@@ -666,70 +784,45 @@ hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int
   }
   // byte offsets inside a tile's buffer resource are 32-bit
   if ((size_t)256 * lda * 2 >= (1u << 31)) return hipErrorInvalidValue;
-  // 256x256 tiles (8 waves of 128x64) once they fill the chip at least twice;
-  // 64x128 tiles (4 waves of 32x64, 48 KB of LDS, up to three workgroups per
-  // CU) when 128x128 tiles would fill at most half of one round of workgroup
-  // slots (two per CU; measured: O-projection and down at M = 1024 4-6%
-  // faster, a 288-tile grid 7% slower); otherwise 128x128 tiles (4 waves of
-  // 64x64, two workgroups per CU)
-  // 8-wave tiles at one workgroup per CU where they fill whole rounds: QKV
-  // 256x192 (waves of 64x96) or 192x384 (96x96), GELU 192x256 (96x64).
-  // The 256x256, 192x256 and 256x192 tiles keep three weight slabs in LDS (W
-  // two slabs ahead, 160, 144 and 136 KB), and so do the 128x128 residual
-  // tiles (80 KB, still two workgroups per CU).  A/B, us: gate/up 330.5 ->
-  // 328.4, ViT fc1 71.1 -> 69.4; with each slab's last k16 step after the
-  // barrier also QKV 196.6 -> 190.7, O-projection 79.8 -> 77.3, down 193.9 ->
-  // 184.9, ViT fc2 68.7 -> 64.9.
-  auto rounds_of = [&](int bm, int bn) -> long {
-    if (N % bn) return 0;
-    const long t = (long)((M + bm - 1) / bm) * (N / bn);
-    return t >= 256 && t % 256 == 0 ? t : 0;
+  // the cheapest tile of the epilogue's set, and the K split of a residual product
+  const int nk = a_parts * K / BK;
+  int best = -1, ns = 1;
+  float best_us = 0.f;
+  auto consider = [&](int i, int splits) {
+    const float us = tile_us(kTiles[i], M, N, nk, splits);
+    if (best < 0 || us < best_us) best = i, ns = splits, best_us = us;
   };
-  if constexpr (std::is_same<Epi, EpiQKV>::value) {
-    if (const long t = rounds_of(256, 192)) {
-      hipLaunchKernelGGL((gemm_bf16_dma_kernel<256, 192, 64, 96, 8, WT, Epi, 3>), dim3((unsigned)t), dim3(512), 0, s,
-                         A, lda, W, M, N, a_parts * K, K, epi);
-      return hipGetLastError();
-    }
-    if (const long t = rounds_of(192, 384)) {
-      hipLaunchKernelGGL((gemm_bf16_dma_kernel<192, 384, 96, 96, 8, WT, Epi>), dim3((unsigned)t), dim3(512), 0, s,
-                         A, lda, W, M, N, a_parts * K, K, epi);
-      return hipGetLastError();
-    }
-  }
-  if constexpr (std::is_same<Epi, EpiGelu>::value) {
-    if (const long t = rounds_of(192, 256)) {
-      hipLaunchKernelGGL((gemm_bf16_dma_kernel<192, 256, 96, 64, 8, WT, Epi, 3>), dim3((unsigned)t), dim3(512), 0, s,
-                         A, lda, W, M, N, a_parts * K, K, epi);
-      return hipGetLastError();
-    }
-  }
-  const long tiles256 = (long)((M + 255) / 256) * ((N + 255) / 256);
-  const long tiles128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-  bool big = false;
-  if constexpr (Epi::kBig) {
-    if (tiles256 >= 512) {
-      big = true;
-      int grid = ((M + 255) / 256) * ((N + 255) / 256);
-      hipLaunchKernelGGL((gemm_bf16_dma_kernel<256, 256, 128, 64, 8, WT, Epi, 3>), dim3(grid), dim3(512), 0, s, A, lda,
-                         W, M, N, a_parts * K, K, epi);
-    }
-  }
-  if (!big && 2 * tiles128 <= 512) {
-    big = true;
-    int grid = ((M + 63) / 64) * ((N + 127) / 128);
-    hipLaunchKernelGGL((gemm_bf16_dma_kernel<64, 128, 32, 64, 4, WT, Epi>), dim3(grid), dim3(256), 0, s, A, lda, W,
-                       M, N, a_parts * K, K, epi);
-  }
-  if (!big) {
-    int grid = ((M + 127) / 128) * ((N + 127) / 128);
+  for (int i = 0; i < T_COUNT; ++i) {
+    if (!tile_allowed<Epi>(i) || (kTiles[i].whole_n && N % kTiles[i].bn)) continue;
+    consider(i, 1);
     if constexpr (std::is_same<Epi, EpiResidual>::value)
-      hipLaunchKernelGGL((gemm_bf16_dma_kernel<128, 128, 64, 64, 4, WT, Epi, 3>), dim3(grid), dim3(256), 0, s, A, lda,
-                         W, M, N, a_parts * K, K, epi);
-    else
-      hipLaunchKernelGGL((gemm_bf16_dma_kernel<128, 128, 64, 64, 4, WT, Epi>), dim3(grid), dim3(256), 0, s, A, lda, W,
-                         M, N, a_parts * K, K, epi);
+      for (int s = 2; s <= 1 + max_parts && s * 4 <= nk; ++s) consider(i, s);
   }
+  Epi e = epi;
+  if constexpr (std::is_same<Epi, EpiResidual>::value) e.ns = ns;
+  if (parts_used) *parts_used = ns - 1;
+  const TileCost& tc = kTiles[best];
+  const dim3 grid((unsigned)((long)((M + tc.bm - 1) / tc.bm) * ((N + tc.bn - 1) / tc.bn) * ns));
+  auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, A, lda, W, M, N, a_parts * K, K, e);
+  };
+#define VLA_TILE(id, nw, ...)                                                            \
+  case id:                                                                               \
+    if constexpr (tile_allowed<Epi>(id)) go(gemm_bf16_dma_kernel<__VA_ARGS__>, 64 * nw); \
+    break
+  switch (best) {
+    VLA_TILE(T_64x64, 4, 64, 64, 32, 32, 4, WT, Epi, 4, 4);
+    VLA_TILE(T_64x128, 4, 64, 128, 32, 64, 4, WT, Epi, 3, 3);
+    VLA_TILE(T_128x128, 8, 128, 128, 32, 64, 8, WT, Epi, 4, 4);
+    VLA_TILE(T_128x128_PAIR, 4, 128, 128, 64, 64, 4, WT, Epi, 3);
+    VLA_TILE(T_256x128, 8, 256, 128, 64, 64, 8, WT, Epi, 3, 3);
+    VLA_TILE(T_256x256, 8, 256, 256, 128, 64, 8, WT, Epi, 3);
+    VLA_TILE(T_256x192, 8, 256, 192, 64, 96, 8, WT, Epi, 3);
+    VLA_TILE(T_192x384, 8, 192, 384, 96, 96, 8, WT, Epi);
+    VLA_TILE(T_192x256, 8, 192, 256, 96, 64, 8, WT, Epi, 3);
+    default: return hipErrorInvalidValue;
+  }
+#undef VLA_TILE
   return hipGetLastError();
 }
 
@@ -741,10 +834,12 @@ hipError_t gemm_bf16_store_f32(const bf16_t* A, int lda, const bf16_t* W, int ld
 }
 
 hipError_t gemm_bf16_residual(const bf16_t* A, int lda, const WOperand& W, float* H, int ldh, const float* bias, int M,
-                              int N, int K, hipStream_t s, int a_parts) {
+                              int N, int K, hipStream_t s, int a_parts, float* part, int max_parts, int* parts_used) {
   // the residual epilogue addresses a wave's rows with 32-bit byte offsets
   if (N % 4 || ldh % 4 || (size_t)256 * ldh * 4 >= (1u << 31)) return hipErrorInvalidValue;
-  return launch<true>(A, lda, W, M, N, K, EpiResidual{H, bias, ldh, M, N}, s, a_parts);
+  EpiResidual e{H, bias, ldh, M, N};
+  e.part = part;
+  return launch<true>(A, lda, W, M, N, K, e, s, a_parts, part && parts_used ? max_parts : 0, parts_used);
 }
 
 hipError_t gemm_bf16_swiglu(const bf16_t* A, int lda, const WOperand& W, bf16_t* out, int ldo, int M, int N, int K,

@@ -37,10 +37,8 @@ def _packed(W, N, K):
     return _dev_bf16(vb.vla_op_pack_weight_bf16(W, N, K))
 
 
-# Tile choices these shapes reach: 128x128 over three quarters of a round
-# (ViT proj / fc2, also over ragged rows), one round of 128x128 (decoder
-# O-projection / down at L=2048), 64x128 (half a round of 128x128), 128x128
-# over ragged rows and columns, single rows.
+# ViT proj / fc2 (also over ragged rows), decoder O-projection / down at
+# L=2048 and L=1024, ragged rows and columns, single rows.
 @pytest.mark.parametrize("M,N,K,bias", [(6144, 1024, 128, True), (6100, 1024, 64, True), (2048, 4096, 192, False),
                                         (1024, 4096, 128, False), (6104, 1000, 192, True), (77, 96, 64, True),
                                         (1, 4, 64, True), (130, 8, 128, False)])
@@ -113,9 +111,8 @@ def _sample_rows(M, tag, n=24):
 
 
 # The products at their full K, in the launch configuration of the bench
-# frame: decoder down (K = 11008, 172 k-slabs) and O-projection (K = 4096) on
-# one round of three-slot 128x128 tiles, ViT fc2 (K = 4096) with its bias;
-# sampled rows against float64.
+# frame: decoder down (K = 11008, 172 k-slabs) and O-projection (K = 4096),
+# ViT fc2 (K = 4096) with its bias; sampled rows against float64.
 @pytest.mark.parametrize("M,N,K,bias", [(2048, 4096, 11008, False), (2048, 4096, 4096, False),
                                         (6144, 1024, 4096, True)])
 def test_gemm_residual_bf16_full_k(M, N, K, bias):
@@ -149,8 +146,8 @@ def test_gemm_residual_bf16_full_k(M, N, K, bias):
     assert e < 1e-5, e
 
 
-# ViT fc1 + GELU at its full K (192x256 three-slot tiles, two whole rounds)
-# and the plain bias product over a two-round 256x256 grid; sampled rows.
+# ViT fc1 + GELU at its full K and the plain bias product over a two-round
+# 256x256 grid; sampled rows.
 @pytest.mark.parametrize("M,N,K,gelu", [(6144, 4096, 1024, True), (2048, 16384, 4096, False)])
 def test_gemm_bias_gelu_bf16_full_k(M, N, K, gelu):
     import torch

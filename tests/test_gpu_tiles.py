@@ -1,0 +1,79 @@
+"""The GEMM's choice of tile and K split over the sizes where it changes, and
+the partial sums a split leaves for the next norm or boundary."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from prefix_cases import EncCase, LlmCase, rel_l2, to_f32
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int16) if a.dtype == np.uint16 else a.copy()).cuda()
+
+
+# K from one slab to past every ring's depth; rows and columns on and off the
+# tile edges of 64, 128 and 256; grids of a few workgroups, about one per CU,
+# about two, and several rounds
+@pytest.mark.parametrize("M,N,K", [(1, 96, 64), (19, 4096, 128), (64, 896, 192), (65, 1152, 256), (130, 4096, 320),
+                                   (203, 1000, 384), (257, 3072, 448), (513, 4096, 512), (1001, 4096, 192),
+                                   (1154, 1024, 1024), (1300, 9728, 128), (2050, 4096, 256)])
+def test_products_over_tiles(M, N, K):
+    import torch
+    from paper_2608_14586_amd import binding as vb
+    A = synth.normal_bf16(synth.seed_of("tileA", M, N, K), (M, K))
+    W = synth.normal_bf16(synth.seed_of("tileW", M, N, K), (N, K))
+    b = synth.normal_f32(synth.seed_of("tileb", M, N, K), (N,))
+    H0 = synth.normal_f32(synth.seed_of("tileH", M, N, K), (M, N))
+    H, out = _dev(H0), torch.empty((M, N), dtype=torch.int16, device="cuda")
+    dA, dW, db = _dev(A), _dev(vb.vla_op_pack_weight_bf16(W, N, K)), _dev(b)
+    vb.vla_op_gemm_residual_bf16(dA, dW, H, db, M, N, K)
+    vb.vla_op_gemm_bias_bf16(dA, dW, out, db, M, N, K, True)
+    torch.cuda.synchronize()
+    a64, w64 = synth.as_f32(A).astype(np.float64), synth.as_f32(W).astype(np.float64)
+    z, mag = a64 @ w64.T + b, np.abs(a64) @ np.abs(w64).T
+    # fp32 accumulation: K / 16 MFMA steps, each one rounding of the running
+    # sum (<= 2^-18 of the sum of |products| for K <= 1024), with a factor 4
+    acc = 2.0 ** -16 * mag + 2.0 ** -22 * (np.abs(z) + np.abs(H0))
+    err = np.abs(H.cpu().numpy() - (H0 + z))
+    assert (err <= acc).all(), np.unravel_index(np.argmax(err - acc), err.shape)
+    ref = oracle.gelu_erf(z)
+    # and one bf16 rounding (2^-9, with a factor 2), GELU's slope (<= 1.13),
+    # and the erfc approximation (1.5e-7 on Phi)
+    err = np.abs(synth.as_f32(out.cpu().numpy().view(np.uint16)) - ref)
+    bound = 2.0 ** -8 * np.abs(ref) + 1.2 * acc + 2e-7 * np.abs(z)
+    assert (err <= bound).all(), np.unravel_index(np.argmax(err - bound), err.shape)
+
+
+@pytest.mark.parametrize("name,L,B", [("small_llm", 1, 1), ("small_llm", 19, 1), ("small_llm", 65, 2),
+                                      ("small_llm", 333, 1), ("llm7b", 33, 1), ("llm7b", 203, 1)])
+def test_split_sums_reach_every_reader(name, L, B):
+    """Few rows: the residual products split K.  The boundary (bf16, fp32),
+    the next block's norm and the KV match the oracle, a run in two ranges is
+    bit for bit one run, and a context with room for more rows splits alike."""
+    k = 2 if name == "small_llm" else 1
+    c = LlmCase(name, L, k, B=B, perturbed=True)
+    tok = c.tokens(frame=4)
+    ref, kv = c.oracle(tok)
+    whole = c.run(tok, frame=1, out_dtype="f32")
+    assert rel_l2(whole.hidden.numpy(), ref) <= 1e-2
+    assert max(rel_l2(to_f32(whole.kv[l]), kv[l]) for l in range(k)) <= 1e-2
+    assert rel_l2(to_f32(c.run(tok, frame=2).hidden), ref) <= 1e-2
+    first = c.run(tok, frame=3, k1=k - 1, out_dtype="f32")
+    second = c.run(first.hidden.numpy().copy(), frame=4, k0=k - 1, out_dtype="f32")
+    assert np.array_equal(second.hidden.numpy(), whole.hidden.numpy())
+    c.close()
+    big = LlmCase(name, L, k, B=B, perturbed=True, max_tokens=1024)
+    assert np.array_equal(big.run(tok, frame=1, out_dtype="f32").hidden.numpy(), whole.hidden.numpy())
+    big.close()
+
+
+@pytest.mark.parametrize("n_img,L", [(1, 50), (2, 131), (1, 257)])
+def test_split_sums_in_the_encoder(n_img, L):
+    c = EncCase("vit_l", n_img, L, n_blocks=2, perturbed=True)
+    p = c.patches(frame=2)
+    assert rel_l2(to_f32(c.run(p)), c.oracle(p)) <= 1e-2
+    c.close()
