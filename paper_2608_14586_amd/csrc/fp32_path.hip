@@ -1,6 +1,6 @@
-// fp32 debug path: the same blocks with no reduced precision anywhere.  Plain
-// VALU kernels; they exist to check the composition (rotary layout, cache
-// layout, grouped heads, residual order) at a 1e-4 bar, not for speed.
+// fp32 debug path: the same blocks with no reduced precision anywhere, to
+// check the composition (rotary layout, cache layout, grouped heads, residual
+// order) at a 1e-4 bar.
 
 #include <math.h>
 
@@ -9,50 +9,80 @@
 namespace vla {
 namespace {
 
-// C = A * W^T (+ bias), or C += ..., 64x64 tile, 16-deep k slabs, 4x4 per thread.
+// C = A * W^T (+ bias), or C += ..., by v_mfma_f32_32x32x2_f32 (fp32 products
+// and sums).  A wave owns a 32x32 tile; per 8 k each lane loads 16 bytes of
+// its A row and of its W row (k range 4 * (lane / 32)), whose four elements
+// feed four MFMAs: element j pairs k = j with k = 4 + j in both operands.  No
+// LDS in the loop: the operands are small and stay in L1 / L2.
+// SPLIT: the four waves take a quarter of K each of one 32x32 tile and add
+// their sums in LDS, so that a product of few tiles still fills the chip and
+// its chain of loads is a quarter as long; otherwise they take the four
+// quadrants of a 64x64 tile.  A 128-row product of the d=256 stack (K = 256
+// and 688) took 57 us with 64x64 VALU tiles in 16-deep LDS slabs (8 to 24
+// workgroups, two barriers a slab) and takes 5.
+// VEC: rows are 16-byte aligned; otherwise elements load one by one.
+template <bool SPLIT, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda,
                                                        const float* __restrict__ W, int ldw, float* __restrict__ C,
                                                        int ldc, const float* __restrict__ bias, int mode, int M,
                                                        int N, int K) {
-  __shared__ float sA[16][64 + 4];
-  __shared__ float sB[16][64 + 4];
-  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int e = tid; e < 64 * 16; e += 256) {
-      int r = e / 16, kk = e % 16;
-      int gm = m0 + r, gn = n0 + r, gk = k0 + kk;
-      sA[kk][r] = (gm < M && gk < K) ? A[(size_t)gm * lda + gk] : 0.f;
-      sB[kk][r] = (gn < N && gk < K) ? W[(size_t)gn * ldw + gk] : 0.f;
-    }
-    __syncthreads();
+  __shared__ float red[SPLIT ? 4 : 1][SPLIT ? 16 : 1][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 31, half = lane >> 5;
+  const int m0 = SPLIT ? blockIdx.y * 32 : blockIdx.y * 64 + (wave >> 1) * 32;
+  const int n0 = SPLIT ? blockIdx.x * 32 : blockIdx.x * 64 + (wave & 1) * 32;
+  // rows past the end load the last row; their results are not stored
+  const float* ar = A + (size_t)min(m0 + li, M - 1) * lda + 4 * half;
+  const float* wr = W + (size_t)min(n0 + li, N - 1) * ldw + 4 * half;
+  const int steps = (K + 7) / 8;
+  const int s0 = SPLIT ? steps * wave / 4 : 0, s1 = SPLIT ? steps * (wave + 1) / 4 : steps;
+  f32x16 acc = {};
+  auto load = [&](const float* r, int s) {
+    const int k = s * 8;
+    if (VEC && k + 8 <= K) return *(const f32x4*)(r + k);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
+    for (int j = 0; j < 4; ++j)
+      if (k + 4 * half + j < K) v[j] = r[k + j];
+    return v;
+  };
+  constexpr int U = 8;
+  int s = s0;
+  for (; s + U <= s1; s += U) {
+    f32x4 a[U], w[U];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sA[kk][ty * 4 + i];
+    for (int u = 0; u < U; ++u) a[u] = load(ar, s + u), w[u] = load(wr, s + u);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = sB[kk][tx * 4 + j];
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][j], w[u][j], acc, 0, 0, 0);
   }
+  for (; s < s1; ++s) {
+    const f32x4 a = load(ar, s), w = load(wr, s);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int row = m0 + ty * 4 + i;
-    if (row >= M) continue;
+    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], w[j], acc, 0, 0, 0);
+  }
+  const int col = n0 + li;
+  const float bv = bias && col < N ? bias[col] : 0.f;
+  auto store = [&](int r, float v) {
+    const int row = m0 + (r >> 2) * 8 + half * 4 + (r & 3);
+    if (row >= M || col >= N) return;
+    float* p = C + (size_t)row * ldc + col;
+    v += bv;
+    *p = mode == 1 ? *p + v : v;
+  };
+  if constexpr (SPLIT) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int col = n0 + tx * 4 + j;
-      if (col >= N) continue;
-      float v = acc[i][j] + (bias ? bias[col] : 0.f);
-      float* p = C + (size_t)row * ldc + col;
-      *p = mode == 1 ? *p + v : v;
+    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = wave * 4 + q;
+      store(r, (red[0][r][lane] + red[1][r][lane]) + (red[2][r][lane] + red[3][r][lane]));
     }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) store(r, acc[r]);
   }
 }
 
@@ -98,48 +128,111 @@ __global__ void qkv_split_f32_kernel(const float* __restrict__ qkv, const float*
   }
 }
 
-// one thread per query; keys streamed through the cache, online softmax
-template <int DHMAX>
-__global__ __launch_bounds__(64) void attention_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                           const float* __restrict__ v, float* __restrict__ o,
-                                                           int B, int H, int Hkv, int L, int dh, int causal,
-                                                           float scale) {
-  const int qi = blockIdx.x * 64 + threadIdx.x;
-  const int h = blockIdx.y, b = blockIdx.z;
-  if (qi >= L) return;
+// 16 queries of one (batch, head) per workgroup, 16 lanes per query; keys in
+// tiles of 64 staged in LDS (rows padded by 16 bytes), online softmax per
+// tile.  A lane scores four keys of its query, and then owns DH / 16 of the
+// query's output dims.  dh <= DH, the dims past it are zeros.  (One thread
+// per query, its q and output rows in registers over all keys, took 844 us at
+// L = 128, 4 heads of 64: eight waves in all, each a serial chain over the
+// keys; this takes 9.)
+constexpr int AF_Q = 16, AF_K = 64;
+template <int DH>
+__global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
+                                                            const float* __restrict__ v, float* __restrict__ o,
+                                                            int B, int H, int Hkv, int L, int dh, int causal,
+                                                            float scale) {
+  constexpr int LD = DH + 4, OD = DH / 16;
+  __shared__ __attribute__((aligned(16))) float sq[AF_Q][LD], sk[AF_K][LD], sv[AF_K][LD], sp[AF_Q][AF_K + 4];
+  const int tid = threadIdx.x, qr = tid >> 4, lq = tid & 15;
+  const int h = blockIdx.y, b = blockIdx.z, q0 = blockIdx.x * AF_Q;
   const int hk = h / (H / Hkv);
-  const float* qr = q + (((size_t)b * H + h) * L + qi) * dh;
+  const float* qh = q + ((size_t)b * H + h) * (size_t)L * dh;
   const float* kh = k + ((size_t)b * Hkv + hk) * (size_t)L * dh;
   const float* vh = v + ((size_t)b * Hkv + hk) * (size_t)L * dh;
-  float qv[DHMAX], acc[DHMAX];
+  // rows [r0, r0 + R) of a head into LDS; rows from L on and dims from dh on are zero
+  auto stage = [&](float (*dst)[LD], const float* src, int r0, int R) {
+    for (int e = tid; e < R * (DH / 4); e += 256) {
+      const int r = e / (DH / 4), d = e % (DH / 4) * 4, row = r0 + r;
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+      if (row < L) {
+        if (dh % 4 == 0) {
+          if (d < dh) x = *(const f32x4*)(src + (size_t)row * dh + d);
+        } else {
 #pragma unroll
-  for (int d = 0; d < DHMAX; ++d) {
-    qv[d] = d < dh ? qr[d] : 0.f;
-    acc[d] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  const int kend = causal ? qi + 1 : L;
-  for (int j = 0; j < kend; ++j) {
-    const float* kr = kh + (size_t)j * dh;
-    float s = 0.f;
+          for (int j = 0; j < 4; ++j)
+            if (d + j < dh) x[j] = src[(size_t)row * dh + d + j];
+        }
+      }
+      *(f32x4*)&dst[r][d] = x;
+    }
+  };
+  stage(sq, qh, q0, AF_Q);
+  const int qi = q0 + qr, kend = causal ? min(L, q0 + AF_Q) : L;
+  float m = -INFINITY, l = 0.f, acc[OD];
 #pragma unroll
-    for (int d = 0; d < DHMAX; ++d)
-      if (d < dh) s = fmaf(qv[d], kr[d], s);
-    s *= scale;
-    float mn = fmaxf(m, s);
-    float alpha = expf(m - mn);
-    float p = expf(s - mn);
-    l = l * alpha + p;
-    const float* vr = vh + (size_t)j * dh;
+  for (int d = 0; d < OD; ++d) acc[d] = 0.f;
+  for (int k0 = 0; k0 < kend; k0 += AF_K) {
+    __syncthreads();  // the previous tile's reads are done
+    stage(sk, kh, k0, AF_K);
+    stage(sv, vh, k0, AF_K);
+    __syncthreads();
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int d = 0; d < DH; d += 4) {
+      const f32x4 x = *(const f32x4*)&sq[qr][d];
 #pragma unroll
-    for (int d = 0; d < DHMAX; ++d)
-      if (d < dh) acc[d] = fmaf(p, vr[d], acc[d] * alpha);
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 y = *(const f32x4*)&sk[lq + 16 * j][d];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[j] = fmaf(x[e], y[e], s[j]);
+      }
+    }
+    float mt = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int key = k0 + lq + 16 * j;
+      s[j] = key < L && (!causal || key <= qi) ? s[j] * scale : -INFINITY;
+      mt = fmaxf(mt, s[j]);
+    }
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) mt = fmaxf(mt, __shfl_xor(mt, off, 16));
+    const float mn = fmaxf(m, mt);
+    // a query past L has no valid key in a causal tile: its row stays empty
+    const float mu = mn == -INFINITY ? 0.f : mn;
+    const float alpha = m == -INFINITY ? 0.f : expf(m - mu);
+    float ps = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float p = s[j] == -INFINITY ? 0.f : expf(s[j] - mu);
+      sp[qr][lq + 16 * j] = p;
+      ps += p;
+    }
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) ps += __shfl_xor(ps, off, 16);
+    l = l * alpha + ps;
     m = mn;
+#pragma unroll
+    for (int d = 0; d < OD; ++d) acc[d] *= alpha;
+    __syncthreads();  // sp
+    for (int j = 0; j < AF_K; ++j) {
+      const float p = sp[qr][j];
+#pragma unroll
+      for (int d = 0; d < OD; d += 4) {
+        const f32x4 x = *(const f32x4*)&sv[j][lq * 4 + d * 16];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[d + e] = fmaf(p, x[e], acc[d + e]);
+      }
+    }
   }
+  if (qi >= L) return;
   float* orow = o + ((size_t)b * L + qi) * (size_t)(H * dh) + h * dh;
 #pragma unroll
-  for (int d = 0; d < DHMAX; ++d)
-    if (d < dh) orow[d] = acc[d] / l;
+  for (int d = 0; d < OD; d += 4)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int c = lq * 4 + d * 16 + e;
+      if (c < dh) orow[c] = acc[d + e] / l;
+    }
 }
 
 __global__ void swiglu_f32_kernel(const float* __restrict__ gu, float* __restrict__ a, int M, int F) {
@@ -162,8 +255,18 @@ __global__ void gelu_f32_kernel(float* x, size_t n) {
 hipError_t gemm_f32(const float* A, int lda, const float* W, int ldw, float* C, int ldc, const float* bias, int mode,
                     int M, int N, int K, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  dim3 grid((N + 63) / 64, (M + 63) / 64);
-  hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, A, lda, W, ldw, C, ldc, bias, mode, M, N, K);
+  // 64x64 tiles once they give every CU a workgroup, split-K 32x32 tiles below
+  const bool split = (long)((M + 63) / 64) * ((N + 63) / 64) < 256;
+  const bool vec = lda % 4 == 0 && ldw % 4 == 0 && ((uintptr_t)A | (uintptr_t)W) % 16 == 0;
+  const int t = split ? 32 : 64;
+  const dim3 grid((N + t - 1) / t, (M + t - 1) / t);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, A, lda, W, ldw, C, ldc, bias, mode, M, N, K);
+  };
+  if (split)
+    vec ? go(gemm_f32_kernel<true, true>) : go(gemm_f32_kernel<true, false>);
+  else
+    vec ? go(gemm_f32_kernel<false, true>) : go(gemm_f32_kernel<false, false>);
   return hipGetLastError();
 }
 
@@ -180,13 +283,13 @@ hipError_t attention_f32(const float* q, const float* k, const float* v, float* 
                          int dh, bool causal, hipStream_t s) {
   if (B <= 0 || L <= 0) return hipSuccess;
   if (Hkv <= 0 || H % Hkv != 0 || dh > 128) return hipErrorInvalidValue;
-  dim3 grid((L + 63) / 64, H, B);
+  dim3 grid((L + AF_Q - 1) / AF_Q, H, B);
   float scale = 1.f / sqrtf((float)dh);
   if (dh <= 64)
-    hipLaunchKernelGGL((attention_f32_kernel<64>), grid, dim3(64), 0, s, q, k, v, o, B, H, Hkv, L, dh, causal ? 1 : 0,
+    hipLaunchKernelGGL((attention_f32_kernel<64>), grid, dim3(256), 0, s, q, k, v, o, B, H, Hkv, L, dh, causal ? 1 : 0,
                        scale);
   else
-    hipLaunchKernelGGL((attention_f32_kernel<128>), grid, dim3(64), 0, s, q, k, v, o, B, H, Hkv, L, dh,
+    hipLaunchKernelGGL((attention_f32_kernel<128>), grid, dim3(256), 0, s, q, k, v, o, B, H, Hkv, L, dh,
                        causal ? 1 : 0, scale);
   return hipGetLastError();
 }

@@ -77,3 +77,30 @@ def test_split_sums_in_the_encoder(n_img, L):
     p = c.patches(frame=2)
     assert rel_l2(to_f32(c.run(p)), c.oracle(p)) <= 1e-2
     c.close()
+
+
+# fp32 path: head dims that are not multiples of 4 or 16, rows that are not
+# 16-byte aligned (odd widths), K and L off the step of 8, the query tile of
+# 16 and the key tile of 64, grouped heads; a grid of 64x64 tiles (the last)
+@pytest.mark.parametrize("d,H,Hkv,dh,F,L,B", [(36, 3, 1, 10, 50, 17, 1), (64, 2, 2, 128, 129, 65, 2),
+                                              (100, 4, 2, 6, 77, 1, 1), (256, 4, 4, 64, 688, 130, 1),
+                                              (132, 2, 1, 66, 31, 16, 3), (512, 8, 2, 64, 8200, 200, 1)])
+def test_fp32_path_odd_shapes(d, H, Hkv, dh, F, L, B):
+    from paper_2608_14586_amd import binding as vb
+    s = synth.configs.llama_like(2, d, H, Hkv, dh, F)
+    wl = synth.Workload("tile_f32_%d_%d" % (d, F), "f32", s, None, batch=B, seq=L)
+    W = [synth.llm_block_weights(wl, l, perturbed=True) for l in range(2)]
+    ctx = vb.Context(llm=vb.stack_cfg(s, "f32", max_tokens=L, max_batch=B))
+    for l in range(2):
+        ctx.vla_load_block_weights(vb.VLA_STACK_LLM, l, W[l])
+    tok = synth.tokens(wl, frame=1)
+    bnd = vb.Boundary(B, L, d, 2, Hkv, dh, stack_dtype="f32", out_dtype="f32")
+    ctx.vla_run_prefix(1, tok, B, L, 2, bnd)
+    ctx.vla_wait_boundary(1, 60000)
+    W64 = [{n: a.astype(np.float64) for n, a in w.items()} for w in W]
+    ref, kv = oracle.run_prefix(tok.astype(np.float64), lambda l: W64[l], s, 2, dtype=np.float64)
+    # fp32 sums of up to 8200 products in chains of a quarter of them: well
+    # under 1e-5; a dropped or doubled element is off by more than 1e-3
+    assert rel_l2(bnd.hidden.numpy(), ref) <= 1e-5
+    assert rel_l2(bnd.kv.numpy(), kv) <= 1e-5
+    ctx.vla_destroy()
