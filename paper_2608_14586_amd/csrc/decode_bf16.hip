@@ -10,6 +10,13 @@
 //    bytes are contiguous per 64-k slab).  The input rows are staged into LDS
 //    once, in bf16, before the main loop: RMSNorm is fused there (QKV,
 //    gate/up; each workgroup recomputes the row's scale, d floats per row).
+//    The rows' loads are issued ahead of the first weights, so that the norm
+//    and the staging run while the weights are on their way, and one sequence
+//    has kernels of its own (a quarter of the accumulators and of the final
+//    reduction).  us a launch, rows behind the weights and four-row kernels
+//    against this, B = 1: 7B QKV 21.3 -> 18.9, gate/up 33.7 -> 32.1, O and
+//    down 13.9 -> 13.3; d=896 QKV 5.1 -> 3.5, gate/up 9.3 -> 8.1, down 6.2 ->
+//    4.8; B = 4: 7B QKV 26.3 -> 24.3.
 //    The gate/up product runs paired: a workgroup owns 16 features' gate
 //    rows and their up rows and writes the gated bf16 activation, which the
 //    down projection stages as it is, like the attention output for the O
@@ -23,13 +30,16 @@
 //    residual add.
 //  * gemv_chunk_kernel: the same product staging the input chunk by chunk
 //    (2048 k at a time, a barrier around each), for inputs too wide for the
-//    streaming kernel's LDS (four rows of a d_ff-wide input) or too short to
-//    fill its chunks.
+//    streaming kernel's LDS (four rows of a d_ff-wide input) or shorter than
+//    half a chunk.  (d=896 products on the streaming kernel: QKV 5.6 -> 5.1
+//    us, and the gate/up product there needs no SwiGLU launch of its own.)
 //  * attn_decode_kernel: one workgroup per (sequence, head, 128-key split);
 //    applies RoPE to q and to the new key at the token's position, appends the
 //    new key and value to the cache, and writes (max, sum, unnormalised
 //    output) partials that a small kernel combines into the bf16 attention
-//    output.  (Combining in the last workgroup of each head, found with a
+//    output -- or, for few heads and splits, the O-projection while it stages
+//    its input (d=896 at position 700: 3.7 + 3.0 us and a launch's gap -> 4.8).
+//     (Combining in the last workgroup of each head, found with a
 //    device-scope counter, needs an L2 write-back per workgroup on this
 //    multi-XCD part and measured 3x slower than the extra launch.)
 // Rounding points follow the prefill: normed activations, q and K/V after
@@ -75,15 +85,97 @@ __device__ __forceinline__ float dot8(const u32x4& w, const u32x4& x, float acc)
   return acc;
 }
 
+__device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+// a buffer resource over one row of `bytes` bytes; a row that is not there
+// has none, so its loads return zeros without memory traffic
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* p, int bytes, bool there = true) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, there ? bytes : 0, 0x00020000);
+}
+
 // ---------------------------------------------------------------- staging
 // Each stage fills xs[b][0..n) (bf16) with columns [k0, k0 + n) of the
 // product's input row b; prepare() runs once before the K loop.
+// The streaming kernel issues the loads of the input rows (preload, into Pre
+// registers; NB rows at most) ahead of its weight loads: loads return in
+// order, so rows loaded behind the weights would be waited for together with
+// them, and the norm's reduction and the LDS fill would follow the weights'
+// arrival instead of running while they are on their way.  Rows too wide for
+// the registers are loaded when they are staged.
 
 // x = bf16(h * rsqrt(mean(h^2) + eps) * g), h fp32 [B][K]
 struct StageNorm {
   const float* h;
   const float* g;
   float eps;
+  static constexpr int PRE = 4;  // 16-byte loads per thread and row: K <= 4096
+  template <int NB>
+  struct Pre {
+    f32x4 h[NB][PRE], g[PRE];
+  };
+  static __device__ __forceinline__ bool preloads(int K) { return K <= PRE * 1024; }
+  template <int NB>
+  __device__ __forceinline__ void preload(Pre<NB>& r, int B, int K, int tid) const {
+    if (!preloads(K)) return;
+    const __amdgpu_buffer_rsrc_t rg = row_rsrc(g, K * 4);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const __amdgpu_buffer_rsrc_t rh = row_rsrc(h + (size_t)min(b, B - 1) * K, K * 4, b < B);
+#pragma unroll
+      for (int j = 0; j < PRE; ++j) r.h[b][j] = __builtin_bit_cast(f32x4, buffer_load16(rh, (tid + 256 * j) * 16));
+    }
+#pragma unroll
+    for (int j = 0; j < PRE; ++j) r.g[j] = __builtin_bit_cast(f32x4, buffer_load16(rg, (tid + 256 * j) * 16));
+  }
+  // staged rows from the preloaded registers
+  template <int NB, int P>
+  __device__ __forceinline__ void fill_pre(const Pre<NB>& r, bf16_t* xs, int Kp, const float* sc, int B, int K,
+                                           int tid) const {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (b >= B) break;
+      const float s = sc[b];
+#pragma unroll
+      for (int j = 0; j < PRE; ++j) {
+        const int i = (tid + 256 * j) * 4;
+        if (i >= K) break;
+        f32x4 y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = r.h[b][j][e] * s * r.g[j][e];
+        *(u32x2*)(xs + (size_t)(b * P) * Kp + i) = u32x2{pack_bf2(y[0], y[1]), pack_bf2(y[2], y[3])};
+        if constexpr (P == 2) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = lo_part(y[e]);
+          *(u32x2*)(xs + (size_t)(b * P + 1) * Kp + i) = u32x2{pack_bf2(y[0], y[1]), pack_bf2(y[2], y[3])};
+        }
+      }
+    }
+  }
+  // sc[b] = 1 / rms(h[b]) from the preloaded registers
+  template <int NB>
+  __device__ __forceinline__ void prepare_pre(const Pre<NB>& r, float* sc, int B, int K, int tid, float* red) const {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      float s = 0.f;
+#pragma unroll
+      for (int j = 0; j < PRE; ++j) {
+        const f32x4 v = r.h[b][j];
+        s += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      if ((tid & 63) == 0) red[(tid >> 6) * GV_MB + b] = s;
+    }
+    finish(sc, B, K, tid, red);
+  }
+  __device__ __forceinline__ void finish(float* sc, int B, int K, int tid, const float* red) const {
+    __syncthreads();
+    if (tid < B)
+      sc[tid] = 1.f / sqrtf((red[tid] + red[GV_MB + tid] + red[2 * GV_MB + tid] + red[3 * GV_MB + tid]) / (float)K +
+                            eps);
+    __syncthreads();
+  }
   // sc[b] = 1 / rms(h[b]) for the B rows at once: every row's 16-byte loads
   // are issued before any sum, and one pair of barriers serves all rows
   // (red: 4 x GV_MB floats)
@@ -109,11 +201,7 @@ struct StageNorm {
       for (int o = 32; o > 0; o >>= 1) s[b] += __shfl_xor(s[b], o);
       if ((tid & 63) == 0) red[(tid >> 6) * GV_MB + b] = s[b];
     }
-    __syncthreads();
-    if (tid < B)
-      sc[tid] = 1.f / sqrtf((red[tid] + red[GV_MB + tid] + red[2 * GV_MB + tid] + red[3 * GV_MB + tid]) / (float)K +
-                            eps);
-    __syncthreads();
+    finish(sc, B, K, tid, red);
   }
   // staged row bp = logical row bp / P; with P = 2 rows alternate between
   // the bf16 value (hi) and its remainder bf16(x - hi) (lo)
@@ -146,6 +234,45 @@ struct StageNorm {
 struct StageCopy {
   const bf16_t* a;
   int ld, lo;
+  // 16-byte loads per thread and row: K <= 12288 for one row, 4096 for four
+  template <int NB>
+  struct Pre {
+    static constexpr int N = NB == 1 ? 6 : 2;
+    u32x4 v[NB][2][N];
+  };
+  static __device__ __forceinline__ bool preloads(int) { return true; }
+  template <int NB>
+  __device__ __forceinline__ void preload(Pre<NB>& r, int B, int K, int tid) const {
+    if (K > Pre<NB>::N * 2048) return;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (q && !lo) break;  // no remainder rows
+        const __amdgpu_buffer_rsrc_t ra = row_rsrc(a + (size_t)min(b, B - 1) * ld + q * lo, K * 2, b < B);
+#pragma unroll
+        for (int j = 0; j < Pre<NB>::N; ++j) r.v[b][q][j] = buffer_load16(ra, (tid + 256 * j) * 16);
+      }
+  }
+  template <int NB, int P>
+  __device__ __forceinline__ void fill_pre(const Pre<NB>& r, bf16_t* xs, int Kp, const float* sc, int B, int K,
+                                           int tid) const {
+    if (K > Pre<NB>::N * 2048) {
+      for (int b = 0; b < B * P; ++b) fill_row(xs + (size_t)b * Kp, sc, b / P, b % P, K, tid);
+      return;
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int q = 0; q < P; ++q)
+#pragma unroll
+        for (int j = 0; j < Pre<NB>::N; ++j) {
+          const int i = (tid + 256 * j) * 8;
+          if (b < B && i < K) *(u32x4*)(xs + (size_t)(b * P + q) * Kp + i) = r.v[b][q][j];
+        }
+  }
+  template <int NB>
+  __device__ __forceinline__ void prepare_pre(const Pre<NB>&, float*, int, int, int, float*) const {}
   __device__ void prepare(float*, int, int, int, float*) const {}
   __device__ void fill(bf16_t* xs, const float*, int Bp, int P, int K, int k0, int n, int tid) const {
     for (int bp = 0; bp < Bp; ++bp) {
@@ -159,7 +286,89 @@ struct StageCopy {
   }
 };
 
-
+// x = the attention output, combined while it is staged from the split-key
+// partials part[B][H][ns][2 + dh] that attn_decode_kernel wrote (see
+// combine_kernel, whose launch this saves): every workgroup reads all of
+// them, so it is for few heads and splits (decode_oproj).  The weight of each
+// (row, head, split), 2^(m_s - m) / sum, goes to LDS first.
+constexpr int SC_MAX = 1024;  // weights that fit
+struct StageCombine {
+  const float* part;
+  int H, ns, dh;
+  template <int NB>
+  struct Pre {};
+  static __device__ __forceinline__ bool preloads(int) { return false; }
+  template <int NB>
+  __device__ __forceinline__ void preload(Pre<NB>&, int, int, int) const {}
+  template <int NB, int P>
+  __device__ __forceinline__ void fill_pre(const Pre<NB>&, bf16_t*, int, const float*, int, int, int) const {}
+  template <int NB>
+  __device__ __forceinline__ void prepare_pre(const Pre<NB>&, float*, int, int, int, float*) const {}
+  static __device__ __forceinline__ float* weights() {
+    __shared__ float w[2 * SC_MAX];
+    return w;
+  }
+  // one (row, head, split) per thread: its maximum and sum to LDS, then its
+  // weight from its head's
+  __device__ void prepare(float*, int B, int, int tid, float*) const {
+    float *w = weights(), *ml = w + SC_MAX;
+    const int n = B * H * ns, stride = 2 + dh;
+    for (int i = tid; i < n; i += 256) {
+      w[i] = part[(size_t)i * stride];
+      ml[i] = part[(size_t)i * stride + 1];
+    }
+    __syncthreads();
+    float wt[SC_MAX / 256];
+#pragma unroll
+    for (int u = 0; u < SC_MAX / 256; ++u) {
+      const int i = tid + 256 * u;
+      if (i < n) {
+        const int i0 = i / ns * ns;
+        float m = -INFINITY, l = 0.f;
+        for (int s = 0; s < ns; ++s) m = fmaxf(m, w[i0 + s]);
+        for (int s = 0; s < ns; ++s) l += (w[i0 + s] == -INFINITY ? 0.f : exp2f(w[i0 + s] - m)) * ml[i0 + s];
+        wt[u] = (w[i] == -INFINITY ? 0.f : exp2f(w[i] - m)) / l;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < SC_MAX / 256; ++u)
+      if (tid + 256 * u < n) w[tid + 256 * u] = wt[u];
+    __syncthreads();
+  }
+  // columns i..i+3 of row b (one head: dh % 4 == 0); the loads of eight
+  // splits are in flight together, past the last they repeat it with weight 0
+  __device__ __forceinline__ u32x2 at4(int b, int i) const {
+    const int h = i / dh, d = i - h * dh, stride = 2 + dh;
+    const float* w = weights() + (b * H + h) * ns;
+    const float* p = part + (size_t)(b * H + h) * ns * stride + 2 + d;
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    float x[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < ns; s0 += 8) {
+      f32x2 v[8][2];
+      float ws[8];
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const int si = min(s0 + s, ns - 1);
+        v[s][0] = *(const f32x2*)(p + si * stride);  // rows of 2 + dh floats: 8-byte aligned
+        v[s][1] = *(const f32x2*)(p + si * stride + 2);
+        ws[s] = s0 + s < ns ? w[si] : 0.f;
+      }
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = fmaf(ws[s], v[s][e / 2][e % 2], x[e]);
+    }
+    return u32x2{pack_bf2(x[0], x[1]), pack_bf2(x[2], x[3])};
+  }
+  __device__ void fill(bf16_t* xs, const float*, int Bp, int, int, int k0, int n, int tid) const {
+    for (int b = 0; b < Bp; ++b)
+      for (int i = tid * 4; i < n; i += 256 * 4) *(u32x2*)(xs + b * GV_KCH + i) = at4(b, k0 + i);
+  }
+  __device__ void fill_row(bf16_t* dst, const float*, int b, int, int K, int tid) const {
+    for (int i = tid * 4; i < K; i += 256 * 4) *(u32x2*)(dst + i) = at4(b, i);
+  }
+};
 
 // a[b][f] = bf16(silu(gate) * up) from the raw gate/up product gu[B][2*fpad]
 // in the packed row order (each group of 64 rows: 32 gate rows, then their 32
@@ -298,25 +507,26 @@ __global__ __launch_bounds__(256) void gemv_chunk_kernel(Stage sg, const bf16_t*
 }
 
 constexpr int GS_KC = 1024;  // k per chunk of the streaming kernel: 16 slabs, 4 per wave
-constexpr int GS_D = 2;      // chunks in flight per lane
 
-__device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-}
+// k per chunk: the paired kernel, twice the rows per lane, keeps the same
+// bytes in flight
+constexpr int stream_kc(bool pair) { return pair ? GS_KC / 2 : GS_KC; }
+
 
 // out[b][n] for n in [blockIdx.x*ROWS, +ROWS), b < B, over the input rows
-// staged whole in LDS (xs[B][Kp], zero past K; Kp a multiple of KC*GS_D).
+// staged whole in LDS (xs[B][Kp], zero past K; Kp a multiple of KC * D).
+// D: chunks in flight per lane.
 // PAIR: the gate/up product with SwiGLU in the epilogue.  Workgroup w owns
 // features [16 w, 16 w + 16): their 16 gate rows and 16 up rows, 32 rows apart
 // in the packed order (each 64-row group: 32 gate rows, then their 32 up
 // rows), and epi(b, f, gate, up) writes the gated activation.
 // Each logical row is staged as P rows (hi, lo with P = 2), B * P <= MB.
-template <int ROWS, bool PAIR, int MB, int P, class Stage, class Epi>
+template <int ROWS, bool PAIR, int MB, int P, int D, class Stage, class Epi>
 __global__ __launch_bounds__(256) void gemv_stream_kernel(Stage sg, const bf16_t* __restrict__ W, int nblk, int N,
                                                           int K, int B, int Kp, Epi epi) {
   static_assert(!PAIR || ROWS == 32, "a paired workgroup owns 16 gate and 16 up rows");
   constexpr int J = ROWS / 8;
-  constexpr int KC = PAIR ? GS_KC / 2 : GS_KC;  // the paired kernel keeps the same bytes in flight
+  constexpr int KC = stream_kc(PAIR);
   constexpr int U = KC / 64 / 4;
   constexpr int SPC = KC / 64;                 // slabs per chunk
   extern __shared__ __attribute__((aligned(16))) bf16_t xs[];
@@ -343,7 +553,7 @@ __global__ __launch_bounds__(256) void gemv_stream_kernel(Stage sg, const bf16_t
   const unsigned slab_stride = (unsigned)nblk * SLAB_N * 64 * 2;
   const unsigned lane_off = (unsigned)(((size_t)blk * SLAB_N + rb) * 64 * 2 + c8 * 16);
   // chunk c, wave w: slabs c*SPC + w + 4u
-  u32x4 wv[GS_D][U][J];
+  u32x4 wv[D][U][J];
   auto issue = [&](int d, int c) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -352,14 +562,24 @@ __global__ __launch_bounds__(256) void gemv_stream_kernel(Stage sg, const bf16_t
       for (int j = 0; j < J; ++j) wv[d][u][j] = buffer_load16(rw, sl * slab_stride + lane_off + roff(j) * 64 * 2);
     }
   };
+  // the input rows' loads first (see the stages), kept ahead of the weights'
+  constexpr int NB = MB / P;
+  typename Stage::template Pre<NB> pre;
+  sg.preload(pre, B, K, tid);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int d = 0; d < GS_D; ++d) issue(d, d);
-  // the input rows (these barriers also give the first chunks time to land)
-  sg.prepare(sc, B, K, tid, tmp);
+  for (int d = 0; d < D; ++d) issue(d, d);
+  __builtin_amdgcn_sched_barrier(0);
+  // stage the rows while the first chunks are on their way
   const int Bp = B * P;
-  for (int b = 0; b < Bp; ++b) {
-    sg.fill_row(xs + (size_t)b * Kp, sc, b / P, b % P, K, tid);
+  for (int b = 0; b < Bp; ++b)
     for (int i = K + tid; i < Kp; i += 256) xs[(size_t)b * Kp + i] = 0;
+  if (Stage::preloads(K)) {
+    sg.prepare_pre(pre, sc, B, K, tid, tmp);
+    sg.template fill_pre<NB, P>(pre, xs, Kp, sc, B, K, tid);
+  } else {
+    sg.prepare(sc, B, K, tid, tmp);
+    for (int b = 0; b < Bp; ++b) sg.fill_row(xs + (size_t)b * Kp, sc, b / P, b % P, K, tid);
   }
   __syncthreads();
   float acc[J][MB];
@@ -368,9 +588,9 @@ __global__ __launch_bounds__(256) void gemv_stream_kernel(Stage sg, const bf16_t
 #pragma unroll
     for (int b = 0; b < MB; ++b) acc[j][b] = 0.f;
   const int nch = Kp / KC;
-  for (int c0 = 0; c0 < nch; c0 += GS_D) {
+  for (int c0 = 0; c0 < nch; c0 += D) {
 #pragma unroll
-    for (int d = 0; d < GS_D; ++d) {
+    for (int d = 0; d < D; ++d) {
       const int c = c0 + d;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -383,7 +603,7 @@ __global__ __launch_bounds__(256) void gemv_stream_kernel(Stage sg, const bf16_t
             for (int j = 0; j < J; ++j) acc[j][b] = dot8(wv[d][u][j], xv, acc[j][b]);
           }
       }
-      issue(d, c + GS_D);  // past the last chunk: reads past K, zero and unused
+      issue(d, c + D);  // past the last chunk: reads past K, zero and unused
     }
   }
   // reduce over the 8 lanes of a row, then over the 4 waves; red row r8 + 8 j
@@ -435,42 +655,57 @@ __global__ __launch_bounds__(256) void gemv_stream_kernel(Stage sg, const bf16_t
   }
 }
 
+// Chunks in flight for a K-wide product: one when K fits it (nothing would
+// fill a second), otherwise two.  (Four for the 8-row workgroups, the whole
+// K of a 7B O-projection, measured slower: O and down 14.3 -> 15.1 us a
+// launch, d=896 down 6.7 -> 7.2.)
+inline int stream_depth(int K, bool pair) { return K <= stream_kc(pair) ? 1 : 2; }
 // the streaming kernel's input rows: B * Kp bf16 in LDS
-inline int stream_kp(int K) { return (K + GS_KC * GS_D - 1) / (GS_KC * GS_D) * (GS_KC * GS_D); }
+inline int stream_kp(int K, bool pair, int depth) {
+  const int c = stream_kc(pair) * depth;
+  return (K + c - 1) / c * c;
+}
 // up to 48 KB the kernel runs several workgroups per CU; up to 96 KB (four
 // d_ff-wide rows) one, and the grid then takes 16-row workgroups once 256 of
-// them fill the CUs
+// them fill the CUs.  Widths below half a chunk keep the chunked kernel.
 constexpr size_t GS_LDS_SHARED = 48 * 1024, GS_LDS_MAX = 96 * 1024;
-inline bool use_stream(int K, int B) { return K >= GS_KC && (size_t)B * stream_kp(K) * 2 <= GS_LDS_MAX; }
+inline bool use_stream(int K, int B) {
+  return K >= GS_KC / 2 && (size_t)B * stream_kp(K, false, 2) * 2 <= GS_LDS_MAX;
+}
 // dynamic LDS above the 64 KB default needs the kernel's attribute raised
 template <class F>
 hipError_t allow_lds(F* kernel, size_t bytes) {
   if (bytes <= 64 * 1024) return hipSuccess;
   return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
-// the buffer resource's size and the offsets (up to 16 slabs past Kp) fit in 31 bits
-inline bool stream_offsets_ok(const WOperand& W, int Kp) {
-  return (size_t)(Kp / 64 + 16) * W.nblk * SLAB_N * 64 * 2 < (1ull << 31);
+// the buffer resource's size and the offsets (up to `ahead` slabs past Kp) fit in 31 bits
+inline bool stream_offsets_ok(const WOperand& W, int Kp, int ahead) {
+  return (size_t)(Kp / 64 + ahead) * W.nblk * SLAB_N * 64 * 2 < (1ull << 31);
+}
+
+template <int ROWS, bool PAIR, int MB, int P, int D, class Stage, class Epi>
+hipError_t launch_stream(const Stage& sg, const WOperand& W, int N, int K, int B, const Epi& epi, int grid,
+                         hipStream_t s) {
+  const int Kp = stream_kp(K, PAIR, D);
+  const size_t lds = (size_t)B * P * Kp * 2;
+  if (!stream_offsets_ok(W, Kp, D * stream_kc(PAIR) / 64) || lds > GS_LDS_MAX) return hipErrorInvalidValue;
+  hipError_t e = allow_lds(gemv_stream_kernel<ROWS, PAIR, MB, P, D, Stage, Epi>, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((gemv_stream_kernel<ROWS, PAIR, MB, P, D, Stage, Epi>), dim3(grid), dim3(256), lds, s, sg, W.p,
+                     W.nblk, N, K, B, Kp, epi);
+  return hipGetLastError();
 }
 
 // B logical rows, each staged as P rows (P = 2: split operands), B * P <= MB
 template <int MB, int P, class Stage, class Epi>
 hipError_t gemv_stream(const Stage& sg, const WOperand& W, int N, int K, int B, const Epi& epi, hipStream_t s) {
-  const int Kp = stream_kp(K);
-  const size_t lds = (size_t)B * P * Kp * 2;
-  if (!stream_offsets_ok(W, Kp)) return hipErrorInvalidValue;
-  if ((N + 15) / 16 >= (lds > GS_LDS_SHARED ? 256 : 512)) {
-    hipError_t e = allow_lds(gemv_stream_kernel<16, false, MB, P, Stage, Epi>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gemv_stream_kernel<16, false, MB, P, Stage, Epi>), dim3((N + 15) / 16), dim3(256), lds, s, sg,
-                       W.p, W.nblk, N, K, B, Kp, epi);
-  } else {
-    hipError_t e = allow_lds(gemv_stream_kernel<8, false, MB, P, Stage, Epi>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gemv_stream_kernel<8, false, MB, P, Stage, Epi>), dim3((N + 7) / 8), dim3(256), lds, s, sg,
-                       W.p, W.nblk, N, K, B, Kp, epi);
-  }
-  return hipGetLastError();
+  const int D = stream_depth(K, false);
+  const size_t lds = (size_t)B * P * stream_kp(K, false, D) * 2;
+  if ((N + 15) / 16 >= (lds > GS_LDS_SHARED ? 256 : 512))
+    return D == 1 ? launch_stream<16, false, MB, P, 1>(sg, W, N, K, B, epi, (N + 15) / 16, s)
+                  : launch_stream<16, false, MB, P, 2>(sg, W, N, K, B, epi, (N + 15) / 16, s);
+  return D == 1 ? launch_stream<8, false, MB, P, 1>(sg, W, N, K, B, epi, (N + 7) / 8, s)
+                : launch_stream<8, false, MB, P, 2>(sg, W, N, K, B, epi, (N + 7) / 8, s);
 }
 
 template <int MB, int P, class Stage, class Epi>
@@ -493,10 +728,14 @@ inline bool gemv_args_ok(const WOperand& W, int N, int K, int B) {
 template <class Stage, class Epi>
 hipError_t gemv(const Stage& sg, const WOperand& W, int N, int K, int B, int parts, const Epi& epi, hipStream_t s) {
   if (!gemv_args_ok(W, N, K, B) || parts < 1 || parts > 2) return hipErrorInvalidValue;
-  if (parts == 2)
-    return use_stream(K, 2 * B) ? gemv_stream<2 * GV_MB, 2>(sg, W, N, K, B, epi, s)
-                                : gemv_chunk<2 * GV_MB, 2>(sg, W, N, K, B, epi, s);
-  return use_stream(K, B) ? gemv_stream<GV_MB, 1>(sg, W, N, K, B, epi, s) : gemv_chunk<GV_MB, 1>(sg, W, N, K, B, epi, s);
+  // one sequence takes kernels of its own: a quarter of the accumulators, of
+  // the final reduction and of the preloaded rows
+  if (parts == 2) {
+    if (!use_stream(K, 2 * B)) return gemv_chunk<2 * GV_MB, 2>(sg, W, N, K, B, epi, s);
+    return B == 1 ? gemv_stream<2, 2>(sg, W, N, K, B, epi, s) : gemv_stream<2 * GV_MB, 2>(sg, W, N, K, B, epi, s);
+  }
+  if (!use_stream(K, B)) return gemv_chunk<GV_MB, 1>(sg, W, N, K, B, epi, s);
+  return B == 1 ? gemv_stream<1, 1>(sg, W, N, K, B, epi, s) : gemv_stream<GV_MB, 1>(sg, W, N, K, B, epi, s);
 }
 
 // packed QKV row of true dimension d of a head (the packing keeps every
@@ -714,6 +953,15 @@ size_t decode_attention_scratch(int B, int H, int dh, int pos) {
   return (size_t)B * H * (pos / ATT_KC + 1) * (2 + dh) * sizeof(float);
 }
 
+// Whether the O-projection combines the split-key partials itself: its N / 8
+// workgroups each read all of them, against one more launch (about 4 us with
+// its gap).  The line lies at 16 MB of reads: d=896, 14 heads of 64 up to
+// position ~5000; 32 heads of 128 only at the first 128 positions.
+bool combine_in_oproj(int B, int H, int dh, int pos, int N) {
+  const size_t ns = pos / ATT_KC + 1, w = (size_t)B * H * ns;
+  return w <= (size_t)SC_MAX && w * (2 + dh) * 4 * (size_t)((N + 7) / 8) <= ((size_t)16 << 20);
+}
+
 hipError_t decode_attention(const float* qkv, int qkv_n, const float* rope_cos, const float* rope_sin, bf16_t* kc,
                             bf16_t* vc, int L_cap, int pos, int B, int H, int Hkv, int dh, float* part, bf16_t* o,
                             hipStream_t s) {
@@ -729,7 +977,7 @@ hipError_t decode_attention(const float* qkv, int qkv_n, const float* rope_cos, 
   else
     return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || !o) return e;
   if (dh == 128)
     hipLaunchKernelGGL((combine_kernel<128>), dim3(B * H), dim3(128), 0, s, part, ns, o);
   else
@@ -739,6 +987,13 @@ hipError_t decode_attention(const float* qkv, int qkv_n, const float* rope_cos, 
 
 hipError_t decode_oproj(const bf16_t* o, int K, const WOperand& W, float* h, int B, int N, hipStream_t s) {
   return gemv(StageCopy{o, K, 0}, W, N, K, B, 1, EpiAdd{h, N}, s);
+}
+
+hipError_t decode_oproj_combine(const float* part, int H, int dh, int pos, const WOperand& W, float* h, int B, int N,
+                                hipStream_t s) {
+  const int ns = pos / ATT_KC + 1;
+  if ((size_t)B * H * ns > (size_t)SC_MAX) return hipErrorInvalidValue;
+  return gemv(StageCombine{part, H, ns, dh}, W, N, H * dh, B, 1, EpiAdd{h, N}, s);
 }
 
 namespace {
@@ -751,14 +1006,9 @@ hipError_t decode_up_impl(const float* h, const float* g, float eps, const WOper
   const EpiGated epi{a, P * fpad, (P - 1) * fpad};
   if (use_stream(K, B * P)) {
     // SwiGLU in the product's epilogue, 16 features per workgroup
-    const int Kp = stream_kp(K);
-    if (!stream_offsets_ok(W, Kp)) return hipErrorInvalidValue;
-    const size_t lds = (size_t)B * P * Kp * 2;
-    hipError_t e = allow_lds(gemv_stream_kernel<32, true, MB, P, StageNorm, EpiGated>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gemv_stream_kernel<32, true, MB, P, StageNorm, EpiGated>), dim3(fpad / 16), dim3(256), lds, s,
-                       StageNorm{h, g, eps}, W.p, W.nblk, N, K, B, Kp, epi);
-    return hipGetLastError();
+    return stream_depth(K, true) == 1
+               ? launch_stream<32, true, MB, P, 1>(StageNorm{h, g, eps}, W, N, K, B, epi, fpad / 16, s)
+               : launch_stream<32, true, MB, P, 2>(StageNorm{h, g, eps}, W, N, K, B, epi, fpad / 16, s);
   }
   hipError_t e = gemv_chunk<MB, P>(StageNorm{h, g, eps}, W, N, K, B, EpiRaw{gu, N}, s);
   if (e != hipSuccess) return e;
@@ -771,8 +1021,11 @@ hipError_t decode_up_impl(const float* h, const float* g, float eps, const WOper
 hipError_t decode_up(const float* h, const float* g, float eps, const WOperand& W, int fpad, float* gu, bf16_t* a,
                      int B, int K, hipStream_t s, int parts) {
   if (!gemv_args_ok(W, 2 * fpad, K, B) || fpad % 64 || parts < 1 || parts > 2) return hipErrorInvalidValue;
-  return parts == 2 ? decode_up_impl<2 * GV_MB, 2>(h, g, eps, W, fpad, gu, a, B, K, s)
-                    : decode_up_impl<GV_MB, 1>(h, g, eps, W, fpad, gu, a, B, K, s);
+  if (parts == 2)
+    return B == 1 ? decode_up_impl<2, 2>(h, g, eps, W, fpad, gu, a, B, K, s)
+                  : decode_up_impl<2 * GV_MB, 2>(h, g, eps, W, fpad, gu, a, B, K, s);
+  return B == 1 ? decode_up_impl<1, 1>(h, g, eps, W, fpad, gu, a, B, K, s)
+                : decode_up_impl<GV_MB, 1>(h, g, eps, W, fpad, gu, a, B, K, s);
 }
 
 hipError_t decode_down(const bf16_t* a, int fpad, const WOperand& W, float* h, int B, int N, hipStream_t s,

@@ -116,7 +116,8 @@ hipError_t decode_qkv(const float* h, const float* g, float eps, const WOperand&
                       hipStream_t s, int parts = 1);
 // Attention of the token at position pos over cache rows [0, pos] of
 // kc/vc [B][Hkv][L_cap][dh]: RoPE on q and the new key, the new key and value
-// appended at pos, o[B][H*dh] (bf16).  Scratch: split-key partials, fp32,
+// appended at pos, o[B][H*dh] (bf16; NULL: the partials stay uncombined, for
+// decode_oproj_combine).  Scratch: split-key partials, fp32,
 // decode_attention_scratch(B, H, dh, pos) bytes.
 size_t decode_attention_scratch(int B, int H, int dh, int pos);
 hipError_t decode_attention(const float* qkv, int qkv_n, const float* rope_cos, const float* rope_sin, bf16_t* kc,
@@ -124,6 +125,11 @@ hipError_t decode_attention(const float* qkv, int qkv_n, const float* rope_cos, 
                             hipStream_t s);
 // h[b] += o[b] . W^T (the O projection, o [B][K] bf16)
 hipError_t decode_oproj(const bf16_t* o, int K, const WOperand& W, float* h, int B, int N, hipStream_t s);
+// ... combining the attention's split-key partials while it stages its input
+// rows, where combine_in_oproj says that this is the cheaper way
+bool combine_in_oproj(int B, int H, int dh, int pos, int N);
+hipError_t decode_oproj_combine(const float* part, int H, int dh, int pos, const WOperand& W, float* h, int B, int N,
+                                hipStream_t s);
 // a[b] = bf16(swiglu(RMSNorm(h[b]) g . W^T)) over the interleaved gate/up
 // rows (N = 2 fpad), the gated activation [B][parts * fpad] (parts = 2: its
 // remainder in columns [fpad, 2 fpad)); gu [B][2 fpad] fp32 is scratch for
@@ -173,7 +179,7 @@ hipError_t layernorm_merge_f32(const float* x, const float* g, const float* b, f
                                int gh, int gw, int m, int d, hipStream_t s);
 hipError_t bf16_to_f32(const bf16_t* x, float* y, size_t n, hipStream_t s);
 hipError_t f32_to_bf16(const float* x, bf16_t* y, size_t n, hipStream_t s, const Parts& parts = Parts{});
-// y = x + parts (fp32)
+// y = x (+ parts), fp32
 hipError_t f32_sum(const float* x, float* y, size_t n, hipStream_t s, const Parts& parts);
 
 // ------------------------------------------------------------- fp32 debug path

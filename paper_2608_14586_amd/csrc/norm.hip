@@ -275,8 +275,10 @@ hipError_t f32_to_bf16(const float* x, bf16_t* y, size_t n, hipStream_t s, const
 
 hipError_t f32_sum(const float* x, float* y, size_t n, hipStream_t s, const Parts& parts) {
   if (n == 0) return hipSuccess;
-  if (parts.n < 1 || !parts.p) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((f32_store_kernel<float, true>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n, parts);
+  if (parts.n)
+    hipLaunchKernelGGL((f32_store_kernel<float, true>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n, parts);
+  else
+    hipLaunchKernelGGL((f32_store_kernel<float, false>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n, parts);
   return hipGetLastError();
 }
 

@@ -195,6 +195,7 @@ struct Slot {
   uint64_t frame_id = 0;
   bool used = false;
   bool has_kv = false;
+  bool direct = false;  // the boundary was stored to the host by a kernel (decode steps)
   void* kv = nullptr;   // device [n_blocks][2][B][Hkv][L][dh]
   void* hid = nullptr;  // device staging of the boundary
   hipEvent_t ev_start = nullptr, ev_done = nullptr, ev_hid = nullptr, ev_copied = nullptr;
@@ -579,6 +580,17 @@ bool is_pinned_host(const void* p) {
   return a.type == hipMemoryTypeHost;
 }
 
+// The address kernels write pinned host memory at, NULL if there is none or
+// it is not aligned for 16-byte stores.
+void* kernel_ptr(const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return (uintptr_t)a.devicePointer % 16 ? nullptr : a.devicePointer;
+}
+
 bool is_device(const void* p) {
   hipPointerAttribute_t a;
   if (hipPointerGetAttributes(&a, p) != hipSuccess) {
@@ -803,7 +815,7 @@ Status retire_slot(vla_ctx* c, Slot& sl) {
   HIPTRY(hipEventSynchronize(sl.ev_copied));
   FrameTimes t{};
   HIPTRY(hipEventElapsedTime(&t.gpu, sl.ev_start, sl.ev_done));
-  HIPTRY(hipEventElapsedTime(&t.xfer, sl.ev_hid, sl.ev_copied));
+  HIPTRY(hipEventElapsedTime(&t.xfer, sl.direct ? sl.ev_done : sl.ev_hid, sl.ev_copied));
   HIPTRY(hipEventElapsedTime(&t.total, sl.ev_start, sl.ev_copied));
   c->history.put(sl.frame_id, t);
   sl.used = false;
@@ -893,6 +905,7 @@ Status run_blocks(vla_ctx* c, uint64_t frame_id, const void* tokens, vla_dtype i
   c->history.erase(frame_id);
   sl.frame_id = frame_id;
   sl.used = true;
+  sl.direct = false;
   out->frame_id = frame_id;
   st = enqueue_blocks(c, sl, tokens, in_dt, B, L, k0, k1, out);
   return st.code ? abandon_frame(c, sl, st) : OK;
@@ -1016,6 +1029,7 @@ Status decode_step(vla_ctx* c, uint64_t frame_id, const void* x, int B, int pos,
   c->history.erase(frame_id);
   sl.frame_id = frame_id;
   sl.used = true;
+  sl.direct = false;
   out->frame_id = frame_id;
   if (!buf.hid) buf.hid = sl.hid;
   st = enqueue_decode(c, sl, x, B, pos, k, kv_cache, L_cap, out, buf, fixed);
@@ -1047,6 +1061,7 @@ Status enqueue_decode(vla_ctx* c, Slot& sl, const void* x, int B, int pos, int k
   bf16_t* abuf = buf.abuf;
   const size_t layer = (size_t)B * Hkv * L_cap * dh;
   const int P = s.parts();  // split operands (hi + lo) under VLA_PREC_SPLIT
+  const bool combine = vla::combine_in_oproj(B, H, dh, pos, d);
   for (int l = 0; l < k; ++l) {
     const Stack::Block& w = s.blocks[l];
     bf16_t* kc = (bf16_t*)kv_cache + (size_t)l * 2 * layer;
@@ -1054,10 +1069,29 @@ Status enqueue_decode(vla_ctx* c, Slot& sl, const void* x, int B, int pos, int k
     PLAUNCH(c, VLA_STACK_LLM, VLA_K_QKV, vla::decode_qkv(h, w.n1g, cf.norm_eps, Stack::packed(w.w_qkv, s.qkv_n), raw, B, s.qkv_n, d, cs, P));
     PLAUNCH(c, VLA_STACK_LLM, VLA_K_ATTN, vla::decode_attention(raw, s.qkv_n, cf.use_rope ? c->rope_cos : nullptr,
                                                              cf.use_rope ? c->rope_sin : nullptr, kc, vc, L_cap, pos, B,
-                                                             H, Hkv, dh, part, obuf, cs));
-    PLAUNCH(c, VLA_STACK_LLM, VLA_K_OPROJ, vla::decode_oproj(obuf, s.hd, Stack::packed(w.w_o, d), h, B, d, cs));
+                                                             H, Hkv, dh, part, combine ? nullptr : obuf, cs));
+    if (combine)
+      PLAUNCH(c, VLA_STACK_LLM, VLA_K_OPROJ, vla::decode_oproj_combine(part, H, dh, pos, Stack::packed(w.w_o, d), h, B, d, cs));
+    else
+      PLAUNCH(c, VLA_STACK_LLM, VLA_K_OPROJ, vla::decode_oproj(obuf, s.hd, Stack::packed(w.w_o, d), h, B, d, cs));
     PLAUNCH(c, VLA_STACK_LLM, VLA_K_MLP_UP, vla::decode_up(h, w.n2g, cf.norm_eps, Stack::packed(w.w_up, 2 * s.f_pad), s.f_pad, gu, abuf, B, d, cs, P));
     PLAUNCH(c, VLA_STACK_LLM, VLA_K_MLP_DOWN, vla::decode_down(abuf, s.f_pad, Stack::packed(w.w_down, d), h, B, d, cs, P));
+  }
+  // The boundary is a few KB: the cast stores it in the pinned buffer itself,
+  // which saves the copy stream's wait and its copy (0.5B-shaped step, 12
+  // blocks: about 10 us of 490).  ev_done precedes the store, so T_X is the
+  // store's time.
+  if (void* host = kernel_ptr(out->hidden)) {
+    sl.direct = true;
+    HIPTRY(hipEventRecord(sl.ev_done, cs));
+    if (out->out_dtype == VLA_BF16)
+      PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_to_bf16(h, (bf16_t*)host, n, cs));
+    else
+      PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_sum(h, (float*)host, n, cs, vla::Parts{}));
+    HIPTRY(hipEventRecord(sl.ev_copied, cs));
+    // whoever orders itself after the copy stream still follows the handoff
+    HIPTRY(hipStreamWaitEvent(c->copy, sl.ev_copied, 0));
+    return OK;
   }
   if (out->out_dtype == VLA_BF16)
     PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_to_bf16(h, (bf16_t*)buf.hid, n, cs));
