@@ -1531,7 +1531,13 @@ vla_status vla_wait_boundary(vla_ctx* ctx, uint64_t frame_id, int timeout_ms) {
             return finish(ctx, fail(VLA_ERR_TIMEOUT, "frame %llu not done after %d ms", (unsigned long long)frame_id,
                                     timeout_ms));
         }
-        std::this_thread::sleep_for(std::chrono::microseconds(20));
+        // The first 2 ms are polled: a sleep, 20 us asked and 70-80 slept, is
+        // much of a decode step (two 7B blocks: 200 us of kernels); longer
+        // waits, a prefix frame's, leave the core to others.
+        if (std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(2))
+          std::this_thread::yield();
+        else
+          std::this_thread::sleep_for(std::chrono::microseconds(20));
       }
     }
     if (ctx->history.find(frame_id)) return finish(ctx, OK);
