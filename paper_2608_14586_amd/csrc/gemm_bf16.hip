@@ -307,7 +307,7 @@ struct EpiQKV {
     const int dh = q.dh, L = q.L;
     // R tokens x NC/64 column groups x 4 chunks of 8 dims
     constexpr int CH = NC / 16;
-    static_assert(R % 16 == 0, "whole 16-token V^T chunks");
+    static_assert(R % 16 == 0, "whole 16-row V^T items");
 #pragma unroll 2
     for (int j = 0; j < (R * CH + 255) / 256; ++j) {
       const int f = tid + 256 * j, row = f / CH, gsel = (f % CH) >> 2, w = (f & 3) * 8;
@@ -334,40 +334,59 @@ struct EpiQKV {
       *(u32x4*)(dst + d1) = pack8(x10, x11);
       *(u32x4*)(dst + d2) = pack8(x20, x21);
     }
-    // V^T: one (dim, 16 consecutive tokens) chunk per item.  Inside every
-    // 16-token group the columns hold the keys in the order
-    // [0-3, 8-11, 4-7, 12-15] (bits 2 and 3 of the key index swapped), the
-    // order in which the attention's PV product consumes them.
+    // V^T: one (dim, group of 16 tokens) per item, the groups those of the
+    // image's own token index.  Inside a group the columns hold the keys in
+    // the order [0-3, 8-11, 4-7, 12-15] (bits 2 and 3 of the key index
+    // swapped), the order in which the attention's PV product consumes them.
+    // An item takes the groups that begin in its 16 rows (and the one the
+    // piece begins inside): two 16-byte stores for a whole group, 8-byte
+    // stores for the whole quads of a cut one.  Groups of the rows instead,
+    // which meet the image's only where its first row is a multiple of 16,
+    // left a second image of 577 tokens to 2-byte stores: ViT QKV at 2 x 577
+    // 25.4 us, now 16.0 (two ViT blocks at 5 x 333 249 -> 211, two 0.5B blocks
+    // at 4 x 701 336 -> 328).
+    const int j0 = __builtin_amdgcn_readfirstlane(tid >> 6), col = tid & 63;
     for (int gsel = 0; gsel < NC / 64; ++gsel) {
       int kind, head, r;
       const int p = n0 + gsel * 64;
       classify(p, kind, head, r);
       if (kind != 2) continue;
       const int c = r / 64;
-      // R / 16 token chunks x 64 columns, strided over the 256 threads
+      const int d = (col < 32) ? c * 32 + col : dh / 2 + c * 32 + (col - 32);
+      const float* tc = T + gsel * 64 + col;
+      for (int j = j0; j < R / 16; j += 4) {
+        const int rows = min(R, M - m0);
+        int t = j * 16;
+        if (t >= rows) break;
+        int b = (m0 + t) / L, pos = m0 + t - b * L;
+        const int tend = min(t + 16, rows);
+        while (t < tend) {
+          const int a = pos & 15, n = min(16 - a, L - pos);  // to the group's or the image's end
+          if (t == 0 || a == 0) {
+            bf16_t* g = q.vt + (((size_t)b * q.Hkv + head) * dh + d) * q.ldvt + (pos - a);
+            const int e1 = a + min(n, rows - t);
+            const float* tr = tc + (t - a) * NC;  // row of the group's key 0
+            if (e1 - a == 16) {
+              float v[16];
 #pragma unroll
-      for (int f = tid; f < R * 4; f += 256) {
-        const int col = f & 63, t16 = (f >> 6) * 16;
-        const int gr0 = m0 + t16;
-        if (gr0 >= M) continue;
-        const int d = (col < 32) ? c * 32 + col : dh / 2 + c * 32 + (col - 32);
-        float v[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = T[(t16 + e) * NC + gsel * 64 + col];
-        const int b0 = gr0 / L, pos0 = gr0 - b0 * L;
-        bf16_t* row = q.vt + (((size_t)b0 * q.Hkv + head) * dh + d) * q.ldvt;
-        if (gr0 + 15 < M && pos0 + 15 < L && (pos0 & 15) == 0 && (q.ldvt & 15) == 0) {
-          *(u32x4*)(row + pos0) = u32x4{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[8], v[9]), pack_bf2(v[10], v[11])};
-          *(u32x4*)(row + pos0 + 8) = u32x4{pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7]), pack_bf2(v[12], v[13]), pack_bf2(v[14], v[15])};
-        } else {
-          int bb = b0, pp = pos0;
-          for (int e = 0; e < 16 && gr0 + e < M; ++e) {
-            const int sw = (pp & ~12) | ((pp & 4) << 1) | ((pp & 8) >> 1);
-            q.vt[(((size_t)bb * q.Hkv + head) * dh + d) * q.ldvt + sw] = f2bf(v[e]);
-            if (++pp == L) {
-              pp = 0;
-              ++bb;
+              for (int e = 0; e < 16; ++e) v[e] = tr[e * NC];
+              *(u32x4*)g = u32x4{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[8], v[9]), pack_bf2(v[10], v[11])};
+              *(u32x4*)(g + 8) = u32x4{pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7]), pack_bf2(v[12], v[13]), pack_bf2(v[14], v[15])};
+            } else {
+              for (int e = a & ~3; e < e1; e += 4) {
+                bf16_t* gq = g + ((e & 4) << 1 | (e & 8) >> 1);
+                if (e >= a && e + 4 <= e1)
+                  *(u32x2*)gq = u32x2{pack_bf2(tr[e * NC], tr[(e + 1) * NC]), pack_bf2(tr[(e + 2) * NC], tr[(e + 3) * NC])};
+                else
+                  for (int i = max(e, a); i < min(e + 4, e1); ++i) gq[i - e] = f2bf(tr[i * NC]);
+              }
             }
+          }
+          t += n;
+          pos += n;
+          if (pos == L) {
+            pos = 0;
+            ++b;
           }
         }
       }

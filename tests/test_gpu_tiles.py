@@ -104,3 +104,34 @@ def test_fp32_path_odd_shapes(d, H, Hkv, dh, F, L, B):
     assert rel_l2(bnd.hidden.numpy(), ref) <= 1e-5
     assert rel_l2(bnd.kv.numpy(), kv) <= 1e-5
     ctx.vla_destroy()
+
+
+# Several sequences in one call, of lengths that are not multiples of 16 (or of
+# the quad, or shorter than a group): the V^T groups of a sequence are cut by
+# tiles and by its neighbours.  Products too short to split K, so every row's
+# sums run in one order and each sequence is bit for bit its own call.
+@pytest.mark.parametrize("L,B", [(1, 4), (3, 4), (15, 3), (16, 4), (17, 4), (31, 3), (50, 4), (66, 4), (77, 3),
+                                 (130, 4), (333, 2)])
+def test_sequences_side_by_side(L, B):
+    import torch
+    from paper_2608_14586_amd import binding as vb
+    s = synth.configs.llama_like(2, 256, 4, 2, 64, 384)
+    wl = synth.Workload("tile_seqs", "bf16", s, None, batch=B, seq=L)
+    ctx = vb.Context(llm=vb.stack_cfg(s, "bf16", max_tokens=L, max_batch=B))
+    for l in range(2):
+        ctx.vla_load_block_weights(vb.VLA_STACK_LLM, l, synth.llm_block_weights(wl, l, perturbed=True))
+    tok = synth.tokens(wl, frame=1)
+
+    def run(frame, t, n):
+        bnd = vb.Boundary(n, L, 256, 2, 2, 64, stack_dtype="bf16", out_dtype="f32")
+        ctx.vla_run_prefix(frame, t, n, L, 2, bnd)
+        ctx.vla_wait_boundary(frame, 60000)
+        return bnd.hidden.numpy().copy(), bnd.kv.view(torch.int16).numpy().copy()
+
+    hid, kv = run(1, tok, B)
+    assert np.isfinite(hid).all()
+    for b in range(B):
+        h1, kv1 = run(2 + b, np.ascontiguousarray(tok[b:b + 1]), 1)
+        assert np.array_equal(h1[0], hid[b]), (b, np.argwhere(h1[0] != hid[b])[:3])
+        assert np.array_equal(kv1[:, :, 0], kv[:, :, b]), b
+    ctx.vla_destroy()
