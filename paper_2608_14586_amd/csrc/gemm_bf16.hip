@@ -743,7 +743,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
 // so the small tiles keep a ring of 3-4 slabs of both operands; large grids
 // are bound by L2 -> LDS traffic and want the large tiles.
 enum TileId {
-  T_64x64, T_64x128, T_128x128, T_128x128_PAIR, T_256x128, T_256x256, T_256x192, T_192x384, T_192x256, T_COUNT
+  T_64x64, T_64x128, T_128x128, T_128x128_PAIR, T_256x128, T_256x256, T_256x192, T_192x384, T_192x256, T_192x128, T_COUNT
 };
 struct TileCost {
   int bm, bn, per_cu;
@@ -760,6 +760,13 @@ constexpr TileCost kTiles[T_COUNT] = {
     {256, 192, 1, true, 1.05f, 1.28f, 0.f, 10.f},      // 136 KB (QKV)
     {192, 384, 1, true, 1.4f, 1.8f, 0.f, 20.f},        // 144 KB (QKV)
     {192, 256, 1, true, 0.9f, 1.15f, 0.f, 11.f},       // 144 KB (GELU)
+    // 120 KB (unsplit: three splits of 576 x 4096, K = 11008 take
+    // 58.1 us as 128x128 and 76.0 so).  One tile per CU where 128x128 gives
+    // half of the CUs two: 6144 x 1024, K = 4096 63.9 -> 54.3 us, 4300 x 1024
+    // 55.2 -> 42.2, 1200 x 4096 49.6 -> 45.7, 1100 x 4096, K = 11008 118 -> 102;
+    // QKV of a 7B block over 300 tokens and the connector over 1536 each about
+    // 13 us less
+    {192, 128, 1, false, 0.32f, 0.71f, 0.f, 8.5f},
 };
 // Estimated us of an M x N product over nk slabs, K split ns ways.  A split
 // writes and reads ns - 1 fp32 partials and rewrites the sum (4 TB/s), and
@@ -783,6 +790,7 @@ constexpr bool tile_allowed(int id) {
          : id == T_256x256 ? Epi::kBig
          : id == T_256x192 || id == T_192x384 ? qkv
          : id == T_192x256 ? gelu
+         : id == T_192x128 ? !Epi::kActInRegs && Epi::kViaLds
                            : true;
 }
 
@@ -815,7 +823,8 @@ hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int
     if (!tile_allowed<Epi>(i) || (kTiles[i].whole_n && N % kTiles[i].bn)) continue;
     consider(i, 1);
     if constexpr (std::is_same<Epi, EpiResidual>::value)
-      for (int s = 2; s <= 1 + max_parts && s * 4 <= nk; ++s) consider(i, s);
+      if (i != T_192x128)
+        for (int s = 2; s <= 1 + max_parts && s * 4 <= nk; ++s) consider(i, s);
   }
   Epi e = epi;
   if constexpr (std::is_same<Epi, EpiResidual>::value) e.ns = ns;
@@ -839,6 +848,7 @@ hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int
     VLA_TILE(T_256x192, 8, 256, 192, 64, 96, 8, WT, Epi, 3);
     VLA_TILE(T_192x384, 8, 192, 384, 96, 96, 8, WT, Epi);
     VLA_TILE(T_192x256, 8, 192, 256, 96, 64, 8, WT, Epi, 3);
+    VLA_TILE(T_192x128, 8, 192, 128, 96, 32, 8, WT, Epi, 3, 3);
     default: return hipErrorInvalidValue;
   }
 #undef VLA_TILE

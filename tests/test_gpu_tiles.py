@@ -135,3 +135,24 @@ def test_sequences_side_by_side(L, B):
         assert np.array_equal(h1[0], hid[b]), (b, np.argwhere(h1[0] != hid[b])[:3])
         assert np.array_equal(kv1[:, :, 0], kv[:, :, b]), b
     ctx.vla_destroy()
+
+
+# 192x128 tiles: long K where they leave one tile per CU, ragged rows, the last
+# tile of columns cut, one row past a tile
+@pytest.mark.parametrize("M,N,K", [(1345, 4000, 4096), (1153, 4096, 4096), (4801, 1024, 4096)])
+def test_residual_192_row_tiles(M, N, K):
+    import torch
+    from paper_2608_14586_amd import binding as vb
+    A = synth.normal_bf16(synth.seed_of("t192A", M, N, K), (M, K))
+    W = synth.normal_bf16(synth.seed_of("t192W", M, N, K), (N, K))
+    H0 = synth.normal_f32(synth.seed_of("t192H", M, N, K), (M, N))
+    H, b = _dev(H0), synth.normal_f32(synth.seed_of("t192b", M, N, K), (N,))
+    vb.vla_op_gemm_residual_bf16(_dev(A), _dev(vb.vla_op_pack_weight_bf16(W, N, K)), H, _dev(b), M, N, K)
+    torch.cuda.synchronize()
+    rows = np.unique(np.r_[0:M:37, 190:194, M - 3:M])
+    a64, w64 = synth.as_f32(A)[rows].astype(np.float64), synth.as_f32(W).astype(np.float64)
+    z, mag = a64 @ w64.T + b, np.abs(a64) @ np.abs(w64).T
+    # K / 16 MFMA steps of one fp32 rounding each (2^-24), with a factor 4
+    acc = K / 16 * 2.0 ** -22 * mag + 2.0 ** -22 * (np.abs(z) + np.abs(H0[rows]))
+    err = np.abs(H.cpu().numpy()[rows] - (H0[rows] + z))
+    assert (err <= acc).all(), np.unravel_index(np.argmax(err - acc), err.shape)
