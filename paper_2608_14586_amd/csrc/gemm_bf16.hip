@@ -413,13 +413,15 @@ __device__ __forceinline__ void buffer_load_lds16(__amdgpu_buffer_rsrc_t r, void
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, 0, 0, 0);
 }
 
+// The launch covers the tiles_n tile columns from column n_base on.
 // K is the k extent of A, Kw that of W (K = Kw or 2 Kw): A's column blocks
 // [0, Kw) and [Kw, 2 Kw) multiply the same W, so an operand carried as
 // a hi + lo pair of bf16 values side by side ([M][2 Kw]) yields
 // hi * W^T + lo * W^T in one accumulator.
 template <int BM, int BN, int WM, int WN, int NW, bool WT, class Epi, int WS = 2, int AS = 2>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __restrict__ A, int lda, WOperand W,
-                                                                int M, int N, int K, int Kw, Epi epi) {
+                                                                int M, int N, int K, int Kw, int n_base, int tiles_n,
+                                                                Epi epi) {
   constexpr int TM = WM / 32, TN = WN / 32;
   constexpr int WAVES_N = BN / WN;
   static_assert((BM / WM) * (BN / WN) == NW, "wave grid must cover the tile");
@@ -444,7 +446,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
 
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int tiles_m = (M + BM - 1) / BM;
   const int nwg = gridDim.x;
   int id = blockIdx.x;
   if ((nwg & 7) == 0) id = (id & 7) * (nwg >> 3) + (id >> 3);
@@ -466,7 +468,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
   const int gsz = min(tiles_m - first_m, GROUP_M);
   const int tile_m = first_m + (id % group) % gsz;
   const int tile_n = (id % group) / gsz;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int m0 = tile_m * BM, n0 = n_base + tile_n * BN;
 
   // buffer resources over the tile's rows; rows past M / N read as zero
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
@@ -794,6 +796,38 @@ constexpr bool tile_allowed(int id) {
                            : true;
 }
 
+// Columns [n0, n1) of the product in tiles of kTiles[id] (K the extent of A,
+// Kw that of W), ns splits of K.
+template <bool WT, class Epi>
+hipError_t launch_tile(int id, const bf16_t* A, int lda, const WOperand& W, int M, int N, int K, int Kw, int n0, int n1,
+                       int ns, const Epi& e, hipStream_t s) {
+  const TileCost& tc = kTiles[id];
+  const int tiles_n = (n1 - n0 + tc.bn - 1) / tc.bn;
+  const dim3 grid((unsigned)((long)((M + tc.bm - 1) / tc.bm) * tiles_n * ns));
+  auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, A, lda, W, M, N, K, Kw, n0, tiles_n, e);
+  };
+#define VLA_TILE(id, nw, ...)                                                            \
+  case id:                                                                               \
+    if constexpr (tile_allowed<Epi>(id)) go(gemm_bf16_dma_kernel<__VA_ARGS__>, 64 * nw); \
+    break
+  switch (id) {
+    VLA_TILE(T_64x64, 4, 64, 64, 32, 32, 4, WT, Epi, 4, 4);
+    VLA_TILE(T_64x128, 4, 64, 128, 32, 64, 4, WT, Epi, 3, 3);
+    VLA_TILE(T_128x128, 8, 128, 128, 32, 64, 8, WT, Epi, 4, 4);
+    VLA_TILE(T_128x128_PAIR, 4, 128, 128, 64, 64, 4, WT, Epi, 3);
+    VLA_TILE(T_256x128, 8, 256, 128, 64, 64, 8, WT, Epi, 3, 3);
+    VLA_TILE(T_256x256, 8, 256, 256, 128, 64, 8, WT, Epi, 3);
+    VLA_TILE(T_256x192, 8, 256, 192, 64, 96, 8, WT, Epi, 3);
+    VLA_TILE(T_192x384, 8, 192, 384, 96, 96, 8, WT, Epi);
+    VLA_TILE(T_192x256, 8, 192, 256, 96, 64, 8, WT, Epi, 3);
+    VLA_TILE(T_192x128, 8, 192, 128, 96, 32, 8, WT, Epi, 3, 3);
+    default: return hipErrorInvalidValue;
+  }
+#undef VLA_TILE
+  return hipGetLastError();
+}
+
 // A [M][a_parts * K]: a_parts column blocks of K, each multiplied by the
 // same W [N][K] into one accumulator (2: a hi + lo operand pair).
 template <bool WT, class Epi>
@@ -826,33 +860,46 @@ hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int
       if (i != T_192x128)
         for (int s = 2; s <= 1 + max_parts && s * 4 <= nk; ++s) consider(i, s);
   }
+  // Two launches: the columns that fill whole rounds of a large tile, and the
+  // rest in the tile that suits them, where the whole in one tile would end
+  // in a round of few workgroups.  Gate/up of a 7B block (22016 columns) over
+  // 1001 tokens is 344 tiles of 256x256, 256 in the first round and 88 in the
+  // second.  The estimate must gain 10 us, what the second launch's drain and
+  // ramp cost (fc1 at 5120 rows, estimated 8 us less, measured 4 us more), and
+  // 3%.  us less a 7B block: 700 tokens 24, 1024 17, 1350 43; with split
+  // operands 700 tokens 53, 1001 35, 1400 86; four 0.5B blocks of 1900 tokens
+  // 39, of 3400 53.  Not where the best tile runs two a CU and only a few are
+  // left for its last round: those start as their CUs come free, and the
+  // estimate has them too dear (0.5B over 1700 tokens, 40 of 512 left: 520 us
+  // in one launch, 528 in two).  A residual product balances its rounds by its
+  // K split instead.
+  int big = -1, n1 = 0, rest = -1;
+  if constexpr (!Epi::kDirect) {
+    float two_us = 0.97f * best_us - 10.f;
+    const TileCost& bc = kTiles[best];
+    if (bc.per_cu == 2 && (long)((M + bc.bm - 1) / bc.bm) * ((N + bc.bn - 1) / bc.bn) % 512 < 64) two_us = 0.f;
+    for (int i = T_256x256; i <= T_192x256; ++i) {
+      const TileCost& c = kTiles[i];
+      if (!tile_allowed<Epi>(i)) continue;
+      const long tm = (M + c.bm - 1) / c.bm, slots = 256L * c.per_cu, rounds = tm * ((N + c.bn - 1) / c.bn) / slots;
+      const long cols = rounds * slots / tm * c.bn;
+      if (cols <= 0 || cols >= N) continue;
+      const float first = tile_us(c, M, (int)cols, nk, 1);
+      for (int j = 0; j < T_COUNT; ++j) {
+        if (!tile_allowed<Epi>(j) || (kTiles[j].whole_n && (N - cols) % kTiles[j].bn)) continue;
+        const float us = first + tile_us(kTiles[j], M, N - (int)cols, nk, 1);
+        if (us < two_us) two_us = us, big = i, n1 = (int)cols, rest = j;
+      }
+    }
+  }
   Epi e = epi;
   if constexpr (std::is_same<Epi, EpiResidual>::value) e.ns = ns;
   if (parts_used) *parts_used = ns - 1;
-  const TileCost& tc = kTiles[best];
-  const dim3 grid((unsigned)((long)((M + tc.bm - 1) / tc.bm) * ((N + tc.bn - 1) / tc.bn) * ns));
-  auto go = [&](auto kernel, int threads) {
-    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, A, lda, W, M, N, a_parts * K, K, e);
-  };
-#define VLA_TILE(id, nw, ...)                                                            \
-  case id:                                                                               \
-    if constexpr (tile_allowed<Epi>(id)) go(gemm_bf16_dma_kernel<__VA_ARGS__>, 64 * nw); \
-    break
-  switch (best) {
-    VLA_TILE(T_64x64, 4, 64, 64, 32, 32, 4, WT, Epi, 4, 4);
-    VLA_TILE(T_64x128, 4, 64, 128, 32, 64, 4, WT, Epi, 3, 3);
-    VLA_TILE(T_128x128, 8, 128, 128, 32, 64, 8, WT, Epi, 4, 4);
-    VLA_TILE(T_128x128_PAIR, 4, 128, 128, 64, 64, 4, WT, Epi, 3);
-    VLA_TILE(T_256x128, 8, 256, 128, 64, 64, 8, WT, Epi, 3, 3);
-    VLA_TILE(T_256x256, 8, 256, 256, 128, 64, 8, WT, Epi, 3);
-    VLA_TILE(T_256x192, 8, 256, 192, 64, 96, 8, WT, Epi, 3);
-    VLA_TILE(T_192x384, 8, 192, 384, 96, 96, 8, WT, Epi);
-    VLA_TILE(T_192x256, 8, 192, 256, 96, 64, 8, WT, Epi, 3);
-    VLA_TILE(T_192x128, 8, 192, 128, 96, 32, 8, WT, Epi, 3, 3);
-    default: return hipErrorInvalidValue;
+  if (big >= 0) {
+    const hipError_t err = launch_tile<WT>(big, A, lda, W, M, N, a_parts * K, K, 0, n1, 1, e, s);
+    return err != hipSuccess ? err : launch_tile<WT>(rest, A, lda, W, M, N, a_parts * K, K, n1, N, 1, e, s);
   }
-#undef VLA_TILE
-  return hipGetLastError();
+  return launch_tile<WT>(best, A, lda, W, M, N, a_parts * K, K, 0, N, ns, e, s);
 }
 
 }  // namespace

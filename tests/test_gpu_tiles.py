@@ -156,3 +156,28 @@ def test_residual_192_row_tiles(M, N, K):
     acc = K / 16 * 2.0 ** -22 * mag + 2.0 ** -22 * (np.abs(z) + np.abs(H0[rows]))
     err = np.abs(H.cpu().numpy()[rows] - (H0[rows] + z))
     assert (err <= acc).all(), np.unravel_index(np.argmax(err - acc), err.shape)
+
+
+# Products in two launches, whole rounds of 256-column tiles and the rest in
+# smaller ones: every column of both, with rows off the tiles.  A column's sums
+# run over K in one order in every tile, so the columns equal, bit for bit,
+# those of a product of the first columns alone (one launch).
+@pytest.mark.parametrize("M,N,K,cut", [(1001, 22016, 4096, 4096), (700, 22016, 4096, 8192), (4206, 4096, 1024, 512)])
+def test_products_in_two_launches(M, N, K, cut):
+    import torch
+    from paper_2608_14586_amd import binding as vb
+    A = synth.normal_bf16(synth.seed_of("twoA", M, N, K), (M, K))
+    W = synth.normal_bf16(synth.seed_of("twoW", M, N, K), (N, K))
+    b = synth.normal_f32(synth.seed_of("twob", M, N, K), (N,))
+    dA = _dev(A)
+
+    def product(n0, n1):
+        out = torch.full((M, n1 - n0), 0x7FC0, dtype=torch.int16, device="cuda")
+        vb.vla_op_gemm_bias_bf16(dA, _dev(vb.vla_op_pack_weight_bf16(np.ascontiguousarray(W[n0:n1]), n1 - n0, K)), out,
+                                 _dev(b[n0:n1]), M, n1 - n0, K, True)
+        torch.cuda.synchronize()
+        return out.cpu().numpy()
+
+    whole = product(0, N)
+    for n0 in list(range(0, N - cut, cut)) + [N - cut]:
+        assert np.array_equal(product(n0, n0 + cut), whole[:, n0:n0 + cut]), n0
