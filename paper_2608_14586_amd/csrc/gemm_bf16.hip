@@ -751,12 +751,17 @@ struct TileCost {
   int bm, bn, per_cu;
   bool whole_n;  // only for N a multiple of bn
   float t0, t1, t2, f;
+  float step = 0.f;  // of t, as the first CU takes a second workgroup
 };
 constexpr TileCost kTiles[T_COUNT] = {
     {64, 64, 2, false, 0.25f, 0.30f, 0.44f, 2.5f},     // 64 KB of LDS
     {64, 128, 2, false, 0.38f, 0.46f, 0.82f, 3.5f},    // 72 KB
     {128, 128, 1, false, 0.38f, 0.55f, 0.f, 5.f},      // 128 KB, 8 waves
-    {128, 128, 2, false, 0.54f, 0.65f, 1.0f, 5.5f},    // 80 KB, 4 waves
+    // 80 KB, 4 waves.  The step: the CUs with two set the time of a round that
+    // gives the others one (gate/up of a 7B block over 203 tokens, 344 tiles,
+    // 0.92 us a slab: 64.2 us, and 53.0 as 172 of 256x128; ViT fc2 at 6144
+    // rows, 384 tiles, 0.91)
+    {128, 128, 2, false, 0.54f, 0.65f, 1.0f, 5.5f, 0.12f},
     {256, 128, 1, false, 0.55f, 0.89f, 0.f, 7.f},      // 144 KB
     {256, 256, 1, false, 1.07f, 1.31f, 0.f, 10.f},     // 160 KB
     {256, 192, 1, true, 1.05f, 1.28f, 0.f, 10.f},      // 136 KB (QKV)
@@ -777,7 +782,8 @@ inline float tile_us(const TileCost& c, int M, int N, int nk, int ns) {
   const long w = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * ns;
   const long slots = 256L * c.per_cu, full = w / slots, rem = w % slots;
   auto round_t = [&](long x) {
-    return x <= 256 ? c.t0 + (c.t1 - c.t0) * (float)x / 256.f : c.t1 + (c.t2 - c.t1) * (float)(x - 256) / 256.f;
+    return x <= 256 ? c.t0 + (c.t1 - c.t0) * (float)x / 256.f
+                    : c.t1 + c.step + (c.t2 - c.t1 - c.step) * (float)(x - 256) / 256.f;
   };
   const float slabs = (float)nk / (float)ns;
   float us = (float)full * (round_t(slots) * slabs + c.f);
