@@ -155,20 +155,6 @@ struct EpiResidual {
   float* H;
   const float* bias;
   int ldh, M, N;
-  // K split over ns workgroups per tile: split 0 adds its sum (and the bias)
-  // to H, split s > 0 stores its sum to part + (s - 1) * M * ldh, which the
-  // reader of H adds.
-  float* part = nullptr;
-  int ns = 1;
-  bool add = true;  // this workgroup's split is 0
-  __device__ __forceinline__ int splits() const { return ns; }
-  __device__ __forceinline__ void select(int split) {
-    if (split > 0) {
-      H = part + (size_t)(split - 1) * M * ldh;
-      bias = nullptr;
-      add = false;
-    }
-  }
   __device__ __forceinline__ const float* park_bias() const { return bias; }
   // One buffer resource over the wave's rows from r0 (rows past M read as
   // zero, stores to them are dropped), one lane offset; rows step by a scalar
@@ -176,15 +162,14 @@ struct EpiResidual {
   // through readfirstlane: the clamp compiles to a vector med3, and a
   // descriptor word in a VGPR would make every access a per-lane (waterfall)
   // loop.
-  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_from(int r0, int nrows, bool any = true) const {
-    const int rows = __builtin_amdgcn_readfirstlane(any ? min(max(M - r0, 0), nrows) : 0);
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_from(int r0, int nrows) const {
+    const int rows = __builtin_amdgcn_readfirstlane(min(max(M - r0, 0), nrows));
     return __builtin_amdgcn_make_buffer_rsrc((void*)(H + (size_t)min(r0, M) * ldh), (short)0, rows * ldh * 4,
                                              0x00020000);
   }
   template <int TM, int TN>
   __device__ void load_acc(f32x16 (&hv)[TM][TN], int r0, int c0, int lane) const {
-    // a split without the residual reads zeros: a resource of no rows
-    const __amdgpu_buffer_rsrc_t rh = rows_from(r0, TM * 32, add);
+    const __amdgpu_buffer_rsrc_t rh = rows_from(r0, TM * 32);
     const int voff = (((lane >> 5) * 4) * ldh + c0 + (lane & 31)) * 4;
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
@@ -450,19 +435,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
   const int nwg = gridDim.x;
   int id = blockIdx.x;
   if ((nwg & 7) == 0) id = (id & 7) * (nwg >> 3) + (id >> 3);
-  // this workgroup's k slabs [kt0, kt0 + nk)
-  int kt0 = 0, nk = K / BK;
-  if constexpr (Epi::kDirect) {
-    const int ns = epi.splits();
-    if (ns > 1) {
-      const int tiles = nwg / ns, split = id / tiles;
-      id -= split * tiles;
-      epi.select(split);
-      const int all = nk;
-      kt0 = split * all / ns;
-      nk = (split + 1) * all / ns - kt0;
-    }
-  }
+  const int nk = K / BK;
   const int group = GROUP_M * tiles_n;
   const int first_m = (id / group) * GROUP_M;
   const int gsz = min(tiles_m - first_m, GROUP_M);
@@ -567,13 +540,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
   };
   int wl = 0, al = 0;  // slots of the last slab
   if constexpr (WS == 2) {
-    issue(kt0 * BK, 0);
+    issue(0, 0);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     frags(0, 0, 0, 0);
     for (int kt = 0; kt + 1 < nk; ++kt) {
       // the other buffer was last read before the previous slab's barrier
-      issue((kt0 + kt + 1) * BK, (kt + 1) & 1);
+      issue((kt + 1) * BK, (kt + 1) & 1);
       slab(kt & 1, kt & 1);
       // the next slab's loads; this wave's fragment reads are consumed
       __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -589,7 +562,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
     constexpr int PER = A_INST + B_INST, LEFT = (AS - 2) * PER;
     static_assert(LEFT < 64, "vmcnt range");
 #pragma unroll
-    for (int i = 0; i < AS - 1; ++i) issue((kt0 + min(i, nk - 1)) * BK, i);
+    for (int i = 0; i < AS - 1; ++i) issue(min(i, nk - 1) * BK, i);
     __builtin_amdgcn_s_waitcnt((LEFT & 15) | ((LEFT >> 4) << 14) | 0x0070);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -597,7 +570,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
     int cs = 0, is = AS - 1;  // slot of slab kt, slot of slab kt - 1
     for (int kt = 0; kt + 1 < nk; ++kt) {
       // slab kt - 1 was last read before the previous barrier
-      issue((kt0 + min(kt + AS - 1, nk - 1)) * BK, is);
+      issue(min(kt + AS - 1, nk - 1) * BK, is);
       head(cs, cs);
       // slab kt + 1 landed; every wave's reads of slab kt are done
       __builtin_amdgcn_s_waitcnt((LEFT & 15) | ((LEFT >> 4) << 14) | 0x0070);
@@ -615,9 +588,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
     // step of each slab runs after the slab barrier, from fragments read
     // before it, and so covers the latency of the next slab's first
     // fragment reads.
-    issue_a(kt0 * BK, 0);
-    issue_w(kt0 * BK, 0);
-    issue_w((kt0 + min(1, nk - 1)) * BK, 1);
+    issue_a(0, 0);
+    issue_w(0, 0);
+    issue_w(min(1, nk - 1) * BK, 1);
     __builtin_amdgcn_s_waitcnt((B_INST & 15) | ((B_INST >> 4) << 14) | 0x0070);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -627,8 +600,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
       // A slot (kt+1)&1 and W slot (kt+2)%3 (slab kt-1) were last read
       // before the previous barrier
       const int wn2 = ws == 0 ? 2 : ws - 1;
-      issue_a((kt0 + kt + 1) * BK, (kt + 1) & 1);
-      issue_w((kt0 + min(kt + 2, nk - 1)) * BK, wn2);
+      issue_a((kt + 1) * BK, (kt + 1) & 1);
+      issue_w(min(kt + 2, nk - 1) * BK, wn2);
       head(kt & 1, ws);
       // A(kt+1) and W(kt+1) landed; W(kt+2) may stay in flight across the
       // barrier; every wave's reads of slab kt are done
@@ -728,18 +701,22 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
 
 // ------------------------------------------------------------ choice of tile
 //
-// A product's tile, and for a residual product the number of K splits, is the
-// one whose estimated time is least.  The estimate: a workgroup spends t us on
-// each of its 64-k slabs and f us on its prologue and epilogue; workgroups run
-// in rounds of 256 (one per CU) or 512 (two per CU), and t grows with the
-// number that run together, since they share L2 and HBM: t0 for few, t1 for
-// one on every CU, t2 for two.  The figures are a least-squares fit to 700
-// timings over M = 19..6144 of the 7B, 0.5B and ViT-L products with their
-// weights read from HBM (mean error 6-11%).  What the choice gives against one
+// A product's tile is the one whose estimated time is least.  K is never
+// split over workgroups: every row's sums run over K in one order in every
+// tile, so a row's bits do not depend on how many rows share the call.  (With
+// K split by the row count a 7B block over 203 tokens took 190 us instead of
+// 200, over 1001 with split operands 750 instead of 783, and a sequence had
+// other bits in a batch than alone.)
+// The estimate: a workgroup spends t us on each of its 64-k slabs and f us on
+// its prologue and epilogue; workgroups run in rounds of 256 (one per CU) or
+// 512 (two per CU), and t grows with the number that run together, since they
+// share L2 and HBM: t0 for few, t1 for one on every CU, t2 for two.  The
+// figures are a least-squares fit to 700 timings over M = 19..6144 of the 7B,
+// 0.5B and ViT-L products with their weights read from HBM (mean error
+// 6-11%).  What the choice gives against one
 // rule on the tile count (64x128 two-slot tiles up to half a round of
 // 128x128, those up to 512 tiles of 256x256), us:
-//   O-projection M=203 50.7 -> 20, M=1001 55.3 -> 38.6, M=2048 71.7 -> 67
-//   down         M=203 127  -> 34 (with the reduction), M=2048 185 -> 161
+//   O-projection M=2048 71.7 -> 67; down M=2048 185 -> 161
 //   7B QKV       M=203 57   -> 38, gate/up M=512 131 -> 90, M=1024 203 -> 171
 // Few workgroups leave each CU waiting on the latency of its own slab loads,
 // so the small tiles keep a ring of 3-4 slabs of both operands; large grids
@@ -767,28 +744,22 @@ constexpr TileCost kTiles[T_COUNT] = {
     {256, 192, 1, true, 1.05f, 1.28f, 0.f, 10.f},      // 136 KB (QKV)
     {192, 384, 1, true, 1.4f, 1.8f, 0.f, 20.f},        // 144 KB (QKV)
     {192, 256, 1, true, 0.9f, 1.15f, 0.f, 11.f},       // 144 KB (GELU)
-    // 120 KB (unsplit: three splits of 576 x 4096, K = 11008 take
-    // 58.1 us as 128x128 and 76.0 so).  One tile per CU where 128x128 gives
-    // half of the CUs two: 6144 x 1024, K = 4096 63.9 -> 54.3 us, 4300 x 1024
+    // 120 KB.  One tile per CU where 128x128 gives half of the CUs two: 6144 x 1024, K = 4096 63.9 -> 54.3 us, 4300 x 1024
     // 55.2 -> 42.2, 1200 x 4096 49.6 -> 45.7, 1100 x 4096, K = 11008 118 -> 102;
     // QKV of a 7B block over 300 tokens and the connector over 1536 each about
     // 13 us less
     {192, 128, 1, false, 0.32f, 0.71f, 0.f, 8.5f},
 };
-// Estimated us of an M x N product over nk slabs, K split ns ways.  A split
-// writes and reads ns - 1 fp32 partials and rewrites the sum (4 TB/s), and
-// adds 2 us to the reader.
-inline float tile_us(const TileCost& c, int M, int N, int nk, int ns) {
-  const long w = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * ns;
+// Estimated us of an M x N product over nk slabs.
+inline float tile_us(const TileCost& c, int M, int N, int nk) {
+  const long w = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
   const long slots = 256L * c.per_cu, full = w / slots, rem = w % slots;
   auto round_t = [&](long x) {
     return x <= 256 ? c.t0 + (c.t1 - c.t0) * (float)x / 256.f
                     : c.t1 + c.step + (c.t2 - c.t1 - c.step) * (float)(x - 256) / 256.f;
   };
-  const float slabs = (float)nk / (float)ns;
-  float us = (float)full * (round_t(slots) * slabs + c.f);
-  if (rem) us += round_t(rem) * slabs + c.f;
-  if (ns > 1) us += 2.f + (float)M * (float)N * (8.f * (ns - 1) + 4.f) / 4.0e6f;
+  float us = (float)full * (round_t(slots) * (float)nk + c.f);
+  if (rem) us += round_t(rem) * (float)nk + c.f;
   return us;
 }
 template <class Epi>
@@ -803,13 +774,13 @@ constexpr bool tile_allowed(int id) {
 }
 
 // Columns [n0, n1) of the product in tiles of kTiles[id] (K the extent of A,
-// Kw that of W), ns splits of K.
+// Kw that of W).
 template <bool WT, class Epi>
 hipError_t launch_tile(int id, const bf16_t* A, int lda, const WOperand& W, int M, int N, int K, int Kw, int n0, int n1,
-                       int ns, const Epi& e, hipStream_t s) {
+                       const Epi& e, hipStream_t s) {
   const TileCost& tc = kTiles[id];
   const int tiles_n = (n1 - n0 + tc.bn - 1) / tc.bn;
-  const dim3 grid((unsigned)((long)((M + tc.bm - 1) / tc.bm) * tiles_n * ns));
+  const dim3 grid((unsigned)((long)((M + tc.bm - 1) / tc.bm) * tiles_n));
   auto go = [&](auto kernel, int threads) {
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, A, lda, W, M, N, K, Kw, n0, tiles_n, e);
   };
@@ -837,9 +808,8 @@ hipError_t launch_tile(int id, const bf16_t* A, int lda, const WOperand& W, int 
 // A [M][a_parts * K]: a_parts column blocks of K, each multiplied by the
 // same W [N][K] into one accumulator (2: a hi + lo operand pair).
 template <bool WT, class Epi>
-hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int K, const Epi& epi, hipStream_t s,
-                  int a_parts = 1, int max_parts = 0, int* parts_used = nullptr) {
-  if (parts_used) *parts_used = 0;
+hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int K, const Epi& e, hipStream_t s,
+                  int a_parts = 1) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (K % BK != 0 || lda % 8 != 0 || a_parts < 1 || a_parts > 2 || lda < a_parts * K) return hipErrorInvalidValue;
   if (WT) {
@@ -851,20 +821,14 @@ hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int
   }
   // byte offsets inside a tile's buffer resource are 32-bit
   if ((size_t)256 * lda * 2 >= (1u << 31)) return hipErrorInvalidValue;
-  // the cheapest tile of the epilogue's set, and the K split of a residual product
+  // the cheapest tile of the epilogue's set
   const int nk = a_parts * K / BK;
-  int best = -1, ns = 1;
+  int best = -1;
   float best_us = 0.f;
-  auto consider = [&](int i, int splits) {
-    const float us = tile_us(kTiles[i], M, N, nk, splits);
-    if (best < 0 || us < best_us) best = i, ns = splits, best_us = us;
-  };
   for (int i = 0; i < T_COUNT; ++i) {
     if (!tile_allowed<Epi>(i) || (kTiles[i].whole_n && N % kTiles[i].bn)) continue;
-    consider(i, 1);
-    if constexpr (std::is_same<Epi, EpiResidual>::value)
-      if (i != T_192x128)
-        for (int s = 2; s <= 1 + max_parts && s * 4 <= nk; ++s) consider(i, s);
+    const float us = tile_us(kTiles[i], M, N, nk);
+    if (best < 0 || us < best_us) best = i, best_us = us;
   }
   // Two launches: the columns that fill whole rounds of a large tile, and the
   // rest in the tile that suits them, where the whole in one tile would end
@@ -877,8 +841,7 @@ hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int
   // 39, of 3400 53.  Not where the best tile runs two a CU and only a few are
   // left for its last round: those start as their CUs come free, and the
   // estimate has them too dear (0.5B over 1700 tokens, 40 of 512 left: 520 us
-  // in one launch, 528 in two).  A residual product balances its rounds by its
-  // K split instead.
+  // in one launch, 528 in two).  Residual products keep to one launch.
   int big = -1, n1 = 0, rest = -1;
   if constexpr (!Epi::kDirect) {
     float two_us = 0.97f * best_us - 10.f;
@@ -890,22 +853,19 @@ hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int
       const long tm = (M + c.bm - 1) / c.bm, slots = 256L * c.per_cu, rounds = tm * ((N + c.bn - 1) / c.bn) / slots;
       const long cols = rounds * slots / tm * c.bn;
       if (cols <= 0 || cols >= N) continue;
-      const float first = tile_us(c, M, (int)cols, nk, 1);
+      const float first = tile_us(c, M, (int)cols, nk);
       for (int j = 0; j < T_COUNT; ++j) {
         if (!tile_allowed<Epi>(j) || (kTiles[j].whole_n && (N - cols) % kTiles[j].bn)) continue;
-        const float us = first + tile_us(kTiles[j], M, N - (int)cols, nk, 1);
+        const float us = first + tile_us(kTiles[j], M, N - (int)cols, nk);
         if (us < two_us) two_us = us, big = i, n1 = (int)cols, rest = j;
       }
     }
   }
-  Epi e = epi;
-  if constexpr (std::is_same<Epi, EpiResidual>::value) e.ns = ns;
-  if (parts_used) *parts_used = ns - 1;
   if (big >= 0) {
-    const hipError_t err = launch_tile<WT>(big, A, lda, W, M, N, a_parts * K, K, 0, n1, 1, e, s);
-    return err != hipSuccess ? err : launch_tile<WT>(rest, A, lda, W, M, N, a_parts * K, K, n1, N, 1, e, s);
+    const hipError_t err = launch_tile<WT>(big, A, lda, W, M, N, a_parts * K, K, 0, n1, e, s);
+    return err != hipSuccess ? err : launch_tile<WT>(rest, A, lda, W, M, N, a_parts * K, K, n1, N, e, s);
   }
-  return launch_tile<WT>(best, A, lda, W, M, N, a_parts * K, K, 0, N, ns, e, s);
+  return launch_tile<WT>(best, A, lda, W, M, N, a_parts * K, K, 0, N, e, s);
 }
 
 }  // namespace
@@ -916,12 +876,10 @@ hipError_t gemm_bf16_store_f32(const bf16_t* A, int lda, const bf16_t* W, int ld
 }
 
 hipError_t gemm_bf16_residual(const bf16_t* A, int lda, const WOperand& W, float* H, int ldh, const float* bias, int M,
-                              int N, int K, hipStream_t s, int a_parts, float* part, int max_parts, int* parts_used) {
+                              int N, int K, hipStream_t s, int a_parts) {
   // the residual epilogue addresses a wave's rows with 32-bit byte offsets
   if (N % 4 || ldh % 4 || (size_t)256 * ldh * 4 >= (1u << 31)) return hipErrorInvalidValue;
-  EpiResidual e{H, bias, ldh, M, N};
-  e.part = part;
-  return launch<true>(A, lda, W, M, N, K, e, s, a_parts, part && parts_used ? max_parts : 0, parts_used);
+  return launch<true>(A, lda, W, M, N, K, EpiResidual{H, bias, ldh, M, N}, s, a_parts);
 }
 
 hipError_t gemm_bf16_swiglu(const bf16_t* A, int lda, const WOperand& W, bf16_t* out, int ldo, int M, int N, int K,

@@ -47,13 +47,9 @@ hipError_t gemm_bf16_store_f32(const bf16_t* A, int lda, const bf16_t* W, int ld
 // A is [M][2K], a hi + lo pair of bf16 values per element side by side
 // (columns [0, K) hi, [K, 2K) lo), and acc = hi * W^T + lo * W^T, twice the
 // MFMA work of a plain bf16 operand and a 16-bit significand in its place.
-// H (fp32 residual) += acc + bias (bias may be NULL).  With `part` (room for
-// max_parts fp32 matrices of M rows of ldh) a product that leaves the chip
-// idle may split K: H then holds the first split's sum and *parts_used
-// matrices at part hold the others', which the next reader of H adds (Parts).
+// H (fp32 residual) += acc + bias (bias may be NULL)
 hipError_t gemm_bf16_residual(const bf16_t* A, int lda, const WOperand& W, float* H, int ldh, const float* bias,
-                              int M, int N, int K, hipStream_t s, int a_parts = 1, float* part = nullptr,
-                              int max_parts = 0, int* parts_used = nullptr);
+                              int M, int N, int K, hipStream_t s, int a_parts = 1);
 // out (bf16) [M][N/2] = silu(gate) * up, W rows interleaved in groups of 32
 // (32 gate rows, then the 32 up rows of the same features); N % 64 == 0.
 // lo_col > 0: the remainder bf16(y - bf16(y)) of each output also goes to
@@ -148,24 +144,13 @@ size_t static_scratch_bytes();
 hipError_t static_scratch_resolve(int device, void** out);
 
 // ----------------------------------------------------- norms and elementwise
-// Partial sums of a split residual product that its reader still has to add:
-// n matrices of the residual's size, one after the other.  Readers form
-// x + ((p[0] + p[1]) + ...), all in the same order; the norms also write that
-// sum back to h (= x).
-struct Parts {
-  const float* p = nullptr;
-  int n = 0;
-  float* h = nullptr;
-};
 // y[M][d] = norm(x[M][d]) (fp32 in); RMSNorm when beta == NULL and !layernorm.
-hipError_t rmsnorm_bf16(const float* x, const float* g, float eps, bf16_t* y, int M, int d, hipStream_t s,
-                         const Parts& parts = Parts{});
+hipError_t rmsnorm_bf16(const float* x, const float* g, float eps, bf16_t* y, int M, int d, hipStream_t s);
 // RMSNorm as a split operand: y[M][2d], columns [0, d) bf16(v), [d, 2d) the
 // remainder bf16(v - bf16(v)) of the fp32 result v.
-hipError_t rmsnorm_bf16_split(const float* x, const float* g, float eps, bf16_t* y, int M, int d, hipStream_t s,
-                         const Parts& parts = Parts{});
+hipError_t rmsnorm_bf16_split(const float* x, const float* g, float eps, bf16_t* y, int M, int d, hipStream_t s);
 hipError_t layernorm_bf16(const float* x, const float* g, const float* b, float eps, bf16_t* y, int M, int d,
-                          hipStream_t s, const Parts& parts = Parts{});
+                          hipStream_t s);
 hipError_t rmsnorm_f32(const float* x, const float* g, float eps, float* y, int M, int d, hipStream_t s);
 hipError_t layernorm_f32(const float* x, const float* g, const float* b, float eps, float* y, int M, int d,
                          hipStream_t s);
@@ -174,13 +159,13 @@ hipError_t layernorm_f32(const float* x, const float* g, const float* b, float e
 // image i becomes feature block (gy % m) * m + gx % m (d wide) of token
 // i * (gh/m) * (gw/m) + (gy/m) * (gw/m) + gx/m (m*m*d wide).
 hipError_t layernorm_merge_bf16(const float* x, const float* g, const float* b, float eps, bf16_t* y, int n_img,
-                                int gh, int gw, int m, int d, hipStream_t s, const Parts& parts = Parts{});
+                                int gh, int gw, int m, int d, hipStream_t s);
 hipError_t layernorm_merge_f32(const float* x, const float* g, const float* b, float eps, float* y, int n_img,
                                int gh, int gw, int m, int d, hipStream_t s);
 hipError_t bf16_to_f32(const bf16_t* x, float* y, size_t n, hipStream_t s);
-hipError_t f32_to_bf16(const float* x, bf16_t* y, size_t n, hipStream_t s, const Parts& parts = Parts{});
-// y = x (+ parts), fp32
-hipError_t f32_sum(const float* x, float* y, size_t n, hipStream_t s, const Parts& parts);
+hipError_t f32_to_bf16(const float* x, bf16_t* y, size_t n, hipStream_t s);
+// y = x, fp32, by a kernel (y may be pinned host memory)
+hipError_t f32_store(const float* x, float* y, size_t n, hipStream_t s);
 
 // ------------------------------------------------------------- fp32 debug path
 // C[M][N] (op) A[M][K] * W[N][K]^T in fp32 FMA; mode 0: C = acc + bias,

@@ -27,13 +27,10 @@ struct RowsMerged {
 
 // lo > 0 (bf16 output only): the remainder bf16(v - bf16(v)) of each output
 // v also goes to y + rows(row) + lo + column.
-// PARTS: the row is x plus the partial sums a split residual product left
-// (Parts), and the sum goes back to parts.h: the reduction costs no launch
-// and no pass over x of its own.
-template <int NCH, bool LAYERNORM, class OutT, class Rows, bool PARTS>
-__global__ __launch_bounds__(256) void norm_kernel(const float* x, const float* __restrict__ g,
+template <int NCH, bool LAYERNORM, class OutT, class Rows>
+__global__ __launch_bounds__(256) void norm_kernel(const float* __restrict__ x, const float* __restrict__ g,
                                                    const float* __restrict__ bta, float eps, OutT* __restrict__ y,
-                                                   int M, int d, Rows rows, int lo, Parts parts) {
+                                                   int M, int d, Rows rows, int lo) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
@@ -54,25 +51,6 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* x, const float* 
     int i = lane + c * 64;
     gv[c] = i < n4 ? g4[i] : f32x4{0.f, 0.f, 0.f, 0.f};
     if constexpr (LAYERNORM) bv[c] = i < n4 ? b4[i] : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  if constexpr (PARTS) {
-    f32x4 t[NCH];
-    for (int p = 0; p < parts.n; ++p) {
-      const f32x4* pr = (const f32x4*)(parts.p + ((size_t)p * M + row) * d);
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int i = lane + c * 64;
-        const f32x4 w = i < n4 ? pr[i] : f32x4{0.f, 0.f, 0.f, 0.f};
-        t[c] = p ? t[c] + w : w;
-      }
-    }
-    f32x4* hr = (f32x4*)(parts.h + (size_t)row * d);
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int i = lane + c * 64;
-      v[c] += t[c];
-      if (i < n4) hr[i] = v[c];
-    }
   }
 #pragma unroll
   for (int c = 0; c < NCH; ++c) s += (v[c][0] + v[c][1]) + (v[c][2] + v[c][3]);
@@ -128,20 +106,13 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* x, const float* 
 
 template <bool LN, class OutT, class Rows>
 hipError_t launch_norm(const float* x, const float* g, const float* b, float eps, OutT* y, int M, int d,
-                       Rows rows, hipStream_t s, int lo = 0, const Parts& parts = Parts{}) {
+                       Rows rows, hipStream_t s, int lo = 0) {
   if (M <= 0) return hipSuccess;
-  if (d % 4 != 0 || parts.n < 0 || (parts.n && (!parts.p || parts.h != x))) return hipErrorInvalidValue;
+  if (d % 4 != 0) return hipErrorInvalidValue;
   const int n4 = d / 4;
   dim3 grid((M + 3) / 4), block(256);
-#define VLA_NORM(NCH)                                                                                               \
-  do {                                                                                                               \
-    if (parts.n)                                                                                                     \
-      hipLaunchKernelGGL((norm_kernel<NCH, LN, OutT, Rows, true>), grid, block, 0, s, x, g, b, eps, y, M, d, rows,   \
-                         lo, parts);                                                                                 \
-    else                                                                                                             \
-      hipLaunchKernelGGL((norm_kernel<NCH, LN, OutT, Rows, false>), grid, block, 0, s, x, g, b, eps, y, M, d, rows,  \
-                         lo, parts);                                                                                 \
-  } while (0)
+#define VLA_NORM(NCH) \
+  hipLaunchKernelGGL((norm_kernel<NCH, LN, OutT, Rows>), grid, block, 0, s, x, g, b, eps, y, M, d, rows, lo)
   if (n4 <= 64) VLA_NORM(1);
   else if (n4 <= 128) VLA_NORM(2);
   else if (n4 <= 256) VLA_NORM(4);
@@ -155,9 +126,9 @@ hipError_t launch_norm(const float* x, const float* g, const float* b, float eps
 
 template <class OutT>
 hipError_t launch_norm_merge(const float* x, const float* g, const float* b, float eps, OutT* y, int n_img, int gh,
-                             int gw, int m, int d, hipStream_t s, const Parts& parts = Parts{}) {
+                             int gw, int m, int d, hipStream_t s) {
   if (n_img <= 0 || gh <= 0 || gw <= 0 || m <= 0 || gh % m || gw % m) return hipErrorInvalidValue;
-  return launch_norm<true>(x, g, b, eps, y, n_img * gh * gw, d, RowsMerged{d, gh, gw, m}, s, 0, parts);
+  return launch_norm<true>(x, g, b, eps, y, n_img * gh * gw, d, RowsMerged{d, gh, gw, m}, s);
 }
 
 __global__ void bf16_to_f32_kernel(const bf16_t* __restrict__ x, float* __restrict__ y, size_t n) {
@@ -182,23 +153,14 @@ __global__ void bf16_to_f32_kernel(const bf16_t* __restrict__ x, float* __restri
   }
 }
 
-// y = x (+ parts), as bf16 or fp32
-template <class OutT, bool PARTS>
-__global__ void f32_store_kernel(const float* __restrict__ x, OutT* __restrict__ y, size_t n, Parts parts) {
+// y = x, as bf16 or fp32
+template <class OutT>
+__global__ void f32_store_kernel(const float* __restrict__ x, OutT* __restrict__ y, size_t n) {
   size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 8;
   size_t stride = (size_t)gridDim.x * blockDim.x * 8;
   for (; i < n; i += stride) {
     if (i + 8 <= n) {
       f32x4 a = *(const f32x4*)(x + i), b = *(const f32x4*)(x + i + 4);
-      if constexpr (PARTS) {
-        f32x4 s = *(const f32x4*)(parts.p + i), t = *(const f32x4*)(parts.p + i + 4);
-        for (int p = 1; p < parts.n; ++p) {
-          s += *(const f32x4*)(parts.p + p * n + i);
-          t += *(const f32x4*)(parts.p + p * n + i + 4);
-        }
-        a += s;
-        b += t;
-      }
       if constexpr (sizeof(OutT) == 2) {
         *(u32x4*)(y + i) = u32x4{pack_bf2(a[0], a[1]), pack_bf2(a[2], a[3]), pack_bf2(b[0], b[1]), pack_bf2(b[2], b[3])};
       } else {
@@ -207,14 +169,8 @@ __global__ void f32_store_kernel(const float* __restrict__ x, OutT* __restrict__
       }
     } else {
       for (size_t j = i; j < n; ++j) {
-        float v = x[j];
-        if constexpr (PARTS) {
-          float s = parts.p[j];
-          for (int p = 1; p < parts.n; ++p) s += parts.p[p * n + j];
-          v += s;
-        }
-        if constexpr (sizeof(OutT) == 2) y[j] = f2bf(v);
-        else y[j] = v;
+        if constexpr (sizeof(OutT) == 2) y[j] = f2bf(x[j]);
+        else y[j] = x[j];
       }
     }
   }
@@ -229,17 +185,15 @@ inline unsigned ew_grid(size_t n) {
 
 }  // namespace
 
-hipError_t rmsnorm_bf16(const float* x, const float* g, float eps, bf16_t* y, int M, int d, hipStream_t s,
-                        const Parts& parts) {
-  return launch_norm<false>(x, g, (const float*)nullptr, eps, y, M, d, RowsPlain{d}, s, 0, parts);
+hipError_t rmsnorm_bf16(const float* x, const float* g, float eps, bf16_t* y, int M, int d, hipStream_t s) {
+  return launch_norm<false>(x, g, (const float*)nullptr, eps, y, M, d, RowsPlain{d}, s);
 }
-hipError_t rmsnorm_bf16_split(const float* x, const float* g, float eps, bf16_t* y, int M, int d, hipStream_t s,
-                              const Parts& parts) {
-  return launch_norm<false>(x, g, (const float*)nullptr, eps, y, M, d, RowsPlain{2 * d}, s, d, parts);
+hipError_t rmsnorm_bf16_split(const float* x, const float* g, float eps, bf16_t* y, int M, int d, hipStream_t s) {
+  return launch_norm<false>(x, g, (const float*)nullptr, eps, y, M, d, RowsPlain{2 * d}, s, d);
 }
 hipError_t layernorm_bf16(const float* x, const float* g, const float* b, float eps, bf16_t* y, int M, int d,
-                          hipStream_t s, const Parts& parts) {
-  return launch_norm<true>(x, g, b, eps, y, M, d, RowsPlain{d}, s, 0, parts);
+                          hipStream_t s) {
+  return launch_norm<true>(x, g, b, eps, y, M, d, RowsPlain{d}, s);
 }
 hipError_t rmsnorm_f32(const float* x, const float* g, float eps, float* y, int M, int d, hipStream_t s) {
   return launch_norm<false>(x, g, (const float*)nullptr, eps, y, M, d, RowsPlain{d}, s);
@@ -250,8 +204,8 @@ hipError_t layernorm_f32(const float* x, const float* g, const float* b, float e
 }
 
 hipError_t layernorm_merge_bf16(const float* x, const float* g, const float* b, float eps, bf16_t* y, int n_img,
-                                int gh, int gw, int m, int d, hipStream_t s, const Parts& parts) {
-  return launch_norm_merge(x, g, b, eps, y, n_img, gh, gw, m, d, s, parts);
+                                int gh, int gw, int m, int d, hipStream_t s) {
+  return launch_norm_merge(x, g, b, eps, y, n_img, gh, gw, m, d, s);
 }
 hipError_t layernorm_merge_f32(const float* x, const float* g, const float* b, float eps, float* y, int n_img,
                                int gh, int gw, int m, int d, hipStream_t s) {
@@ -264,21 +218,15 @@ hipError_t bf16_to_f32(const bf16_t* x, float* y, size_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t f32_to_bf16(const float* x, bf16_t* y, size_t n, hipStream_t s, const Parts& parts) {
+hipError_t f32_to_bf16(const float* x, bf16_t* y, size_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  if (parts.n)
-    hipLaunchKernelGGL((f32_store_kernel<bf16_t, true>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n, parts);
-  else
-    hipLaunchKernelGGL((f32_store_kernel<bf16_t, false>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n, parts);
+  hipLaunchKernelGGL((f32_store_kernel<bf16_t>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n);
   return hipGetLastError();
 }
 
-hipError_t f32_sum(const float* x, float* y, size_t n, hipStream_t s, const Parts& parts) {
+hipError_t f32_store(const float* x, float* y, size_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  if (parts.n)
-    hipLaunchKernelGGL((f32_store_kernel<float, true>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n, parts);
-  else
-    hipLaunchKernelGGL((f32_store_kernel<float, false>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n, parts);
+  hipLaunchKernelGGL((f32_store_kernel<float>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n);
   return hipGetLastError();
 }
 

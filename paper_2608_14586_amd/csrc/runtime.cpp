@@ -25,14 +25,6 @@ thread_local std::string g_last_error;
 constexpr int NSLOT = 3;          // frames that may be in flight at once
 constexpr size_t ALIGN = 256;     // arena sub-allocation alignment
 constexpr size_t HISTORY = 256;   // finished frames whose times are kept
-// Scratch of a bf16 stack's split residual products: up to SPLIT_PARTS fp32
-// partials of the residual, SPLIT_BYTES in all.  Both bounds are taken on the
-// rows of the call, so a context's limits do not change how a product splits.
-constexpr int SPLIT_PARTS = 7;
-constexpr size_t SPLIT_BYTES = (size_t)32 << 20;
-inline int split_parts(int M, int d) {
-  return (int)std::min<size_t>(SPLIT_PARTS, SPLIT_BYTES / ((size_t)M * d * 4));
-}
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int round_up(int x, int a) { return (x + a - 1) / a * a; }
@@ -245,14 +237,6 @@ struct Workspace {
   void* act = nullptr;       // MLP activation
   float* qkv_raw = nullptr;  // fp32 path only
   void* tok = nullptr;       // staging of host-resident inputs
-  float* part = nullptr;     // partial sums of split residual products (bf16)
-  int parts = 0;             // ... of them not yet added to h
-  // what the next reader of h has to add, taken over by that reader
-  vla::Parts take_parts() {
-    const vla::Parts p{part, parts, h};
-    parts = 0;
-    return p;
-  }
 };
 
 }  // namespace
@@ -363,7 +347,6 @@ void layout(vla_ctx* c, Bump& a) {
     w.act = a.take(s->bf16() ? pairs * M * s->f_pad * e : M * (size_t)s->c.d_ff * (s->llm() ? 3 : 1) * 4);
     if (!s->bf16()) w.qkv_raw = (float*)a.take(M * s->qkv_n * 4);
     w.tok = a.take(M * d * e);
-    if (s->bf16()) w.part = (float*)a.take(std::min(SPLIT_BYTES, SPLIT_PARTS * M * d * 4));
   }
   int rope_len = 0, rope_half = 0;
   if (c->llm.present && c->llm.c.use_rope) rope_len = c->llm.c.max_tokens, rope_half = c->llm.c.head_dim / 2;
@@ -704,9 +687,9 @@ Status llm_block_bf16(vla_ctx* c, const Stack::Block& w, int B, int L, bf16_t* k
   Workspace& ws = c->ws[VLA_STACK_LLM];
   const int P = s.parts();
   if (P == 2)
-    PLAUNCH(c, VLA_STACK_LLM, VLA_K_NORM, vla::rmsnorm_bf16_split(ws.h, w.n1g, k.norm_eps, (bf16_t*)ws.x, M, d, st, ws.take_parts()));
+    PLAUNCH(c, VLA_STACK_LLM, VLA_K_NORM, vla::rmsnorm_bf16_split(ws.h, w.n1g, k.norm_eps, (bf16_t*)ws.x, M, d, st));
   else
-    PLAUNCH(c, VLA_STACK_LLM, VLA_K_NORM, vla::rmsnorm_bf16(ws.h, w.n1g, k.norm_eps, (bf16_t*)ws.x, M, d, st, ws.take_parts()));
+    PLAUNCH(c, VLA_STACK_LLM, VLA_K_NORM, vla::rmsnorm_bf16(ws.h, w.n1g, k.norm_eps, (bf16_t*)ws.x, M, d, st));
   vla::QkvArgs qa{nullptr, k.use_rope ? c->rope_cos : nullptr, k.use_rope ? c->rope_sin : nullptr,
                   (bf16_t*)ws.q, kdst, vdst, (bf16_t*)ws.vt, round_up(L, 64), L, k.n_heads, k.n_kv_heads,
                   k.head_dim};
@@ -722,17 +705,16 @@ Status llm_block_bf16_rest(vla_ctx* c, const Stack::Block& w, int B, int L, cons
   Workspace& ws = c->ws[VLA_STACK_LLM];
   PLAUNCH(c, VLA_STACK_LLM, VLA_K_ATTN, vla::attention_bf16((const bf16_t*)ws.q, kdst, (const bf16_t*)ws.vt, round_up(L, 64), (bf16_t*)ws.o, B,
                            k.n_heads, k.n_kv_heads, L, k.head_dim, k.causal != 0, st));
-  PLAUNCH(c, VLA_STACK_LLM, VLA_K_OPROJ, vla::gemm_bf16_residual((const bf16_t*)ws.o, s.hd, Stack::packed(w.w_o, d), ws.h, d, nullptr, M, d, s.hd, st,
-                                                                  1, ws.part, split_parts(M, d), &ws.parts));
+  PLAUNCH(c, VLA_STACK_LLM, VLA_K_OPROJ, vla::gemm_bf16_residual((const bf16_t*)ws.o, s.hd, Stack::packed(w.w_o, d), ws.h, d, nullptr, M, d, s.hd, st));
   const int P = s.parts(), F = s.f_pad;
   if (P == 2)
-    PLAUNCH(c, VLA_STACK_LLM, VLA_K_NORM, vla::rmsnorm_bf16_split(ws.h, w.n2g, k.norm_eps, (bf16_t*)ws.x, M, d, st, ws.take_parts()));
+    PLAUNCH(c, VLA_STACK_LLM, VLA_K_NORM, vla::rmsnorm_bf16_split(ws.h, w.n2g, k.norm_eps, (bf16_t*)ws.x, M, d, st));
   else
-    PLAUNCH(c, VLA_STACK_LLM, VLA_K_NORM, vla::rmsnorm_bf16(ws.h, w.n2g, k.norm_eps, (bf16_t*)ws.x, M, d, st, ws.take_parts()));
+    PLAUNCH(c, VLA_STACK_LLM, VLA_K_NORM, vla::rmsnorm_bf16(ws.h, w.n2g, k.norm_eps, (bf16_t*)ws.x, M, d, st));
   PLAUNCH(c, VLA_STACK_LLM, VLA_K_MLP_UP, vla::gemm_bf16_swiglu((const bf16_t*)ws.x, P * d, Stack::packed(w.w_up, 2 * F), (bf16_t*)ws.act,
                                                                 P * F, M, 2 * F, d, st, P, P == 2 ? F : 0));
   PLAUNCH(c, VLA_STACK_LLM, VLA_K_MLP_DOWN, vla::gemm_bf16_residual((const bf16_t*)ws.act, P * F, Stack::packed(w.w_down, d), ws.h, d, nullptr,
-                                                                    M, d, F, st, P, ws.part, split_parts(M, d), &ws.parts));
+                                                                    M, d, F, st, P));
   return OK;
 }
 
@@ -777,20 +759,19 @@ Status enc_block(vla_ctx* c, const Stack::Block& w, int n_img, int L) {
   Workspace& ws = c->ws[VLA_STACK_ENC];
   if (s.bf16()) {
     bf16_t* x = (bf16_t*)ws.x;
-    PLAUNCH(c, VLA_STACK_ENC, VLA_K_NORM, vla::layernorm_bf16(ws.h, w.n1g, w.n1b, k.norm_eps, x, M, d, st, ws.take_parts()));
+    PLAUNCH(c, VLA_STACK_ENC, VLA_K_NORM, vla::layernorm_bf16(ws.h, w.n1g, w.n1b, k.norm_eps, x, M, d, st));
     vla::QkvArgs qa{w.b_qkv, nullptr, nullptr, (bf16_t*)ws.q, (bf16_t*)ws.ek, nullptr, (bf16_t*)ws.vt,
                     round_up(L, 64), L, k.n_heads, k.n_kv_heads, k.head_dim};
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_QKV, vla::gemm_bf16_qkv(x, d, Stack::packed(w.w_qkv, s.qkv_n), qa, M, s.qkv_n, d, st));
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_ATTN, vla::attention_bf16((const bf16_t*)ws.q, (const bf16_t*)ws.ek, (const bf16_t*)ws.vt, round_up(L, 64),
                              (bf16_t*)ws.o, n_img, k.n_heads, k.n_kv_heads, L, k.head_dim, false, st));
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_OPROJ, vla::gemm_bf16_residual((const bf16_t*)ws.o, s.hd, Stack::packed(w.w_o, d), ws.h, d, w.b_o, M, d,
-                                                            s.hd, st, 1, ws.part, split_parts(M, d), &ws.parts));
-    PLAUNCH(c, VLA_STACK_ENC, VLA_K_NORM, vla::layernorm_bf16(ws.h, w.n2g, w.n2b, k.norm_eps, x, M, d, st, ws.take_parts()));
+                                                            s.hd, st));
+    PLAUNCH(c, VLA_STACK_ENC, VLA_K_NORM, vla::layernorm_bf16(ws.h, w.n2g, w.n2b, k.norm_eps, x, M, d, st));
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_MLP_UP, vla::gemm_bf16_gelu(x, d, Stack::packed(w.w_up, s.f_pad), (bf16_t*)ws.act, s.f_pad, w.b_up, M, s.f_pad,
                                                        d, st));
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_MLP_DOWN, vla::gemm_bf16_residual((const bf16_t*)ws.act, s.f_pad, Stack::packed(w.w_down, d), ws.h, d,
-                                                               w.b_down, M, d, s.f_pad, st, 1, ws.part, split_parts(M, d),
-                                                               &ws.parts));
+                                                               w.b_down, M, d, s.f_pad, st));
   } else {
     float* x = (float*)ws.x;
     const int F = k.d_ff;
@@ -929,9 +910,7 @@ Status enqueue_blocks(vla_ctx* c, Slot& sl, const void* tokens, vla_dtype in_dt,
     HIPTRY(hipEventRecord(c->ev_intake, c->compute));
     c->intake_recorded = true;
   }
-  Workspace& ws = c->ws[VLA_STACK_LLM];
-  float* h = ws.h;
-  ws.parts = 0;  // a frame that failed part-way may have left some
+  float* h = c->ws[VLA_STACK_LLM].h;
   for (int l = k0; l < k1; ++l) {
     const Stack::Block& w = s.blocks[l];
     char* kvl = (char*)sl.kv + (size_t)(l - k0) * layer_elems * s.esz;
@@ -954,9 +933,7 @@ Status enqueue_blocks(vla_ctx* c, Slot& sl, const void* tokens, vla_dtype in_dt,
     if (st.code) return st;
   }
   if (out->out_dtype == VLA_BF16)
-    PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_to_bf16(h, (bf16_t*)sl.hid, n, c->compute, ws.take_parts()));
-  else if (ws.parts)
-    PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_sum(h, (float*)sl.hid, n, c->compute, ws.take_parts()));
+    PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_to_bf16(h, (bf16_t*)sl.hid, n, c->compute));
   else
     HIPTRY(hipMemcpyAsync(sl.hid, h, n * 4, hipMemcpyDeviceToDevice, c->compute));
   HIPTRY(hipEventRecord(sl.ev_done, c->compute));
@@ -1087,7 +1064,7 @@ Status enqueue_decode(vla_ctx* c, Slot& sl, const void* x, int B, int pos, int k
     if (out->out_dtype == VLA_BF16)
       PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_to_bf16(h, (bf16_t*)host, n, cs));
     else
-      PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_sum(h, (float*)host, n, cs, vla::Parts{}));
+      PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_store(h, (float*)host, n, cs));
     HIPTRY(hipEventRecord(sl.ev_copied, cs));
     // whoever orders itself after the copy stream still follows the handoff
     HIPTRY(hipStreamWaitEvent(c->copy, sl.ev_copied, 0));
@@ -1117,8 +1094,6 @@ Status run_encoder(vla_ctx* c, const void* patches, int n_img, int L, void* out_
     if (!s.blocks[l].loaded) return fail(VLA_ERR_NOT_LOADED, "encoder block %d has no weights", l);
   if (!is_device(out_dev)) return fail(VLA_ERR_INVALID_ARG, "encoder output must be device memory");
   const size_t n = (size_t)n_img * L * s.c.d_model;
-  Workspace& ws = c->ws[VLA_STACK_ENC];
-  ws.parts = 0;  // a run that failed part-way may have left some
   Status st = intake(c, VLA_STACK_ENC, s.c.dtype, patches, n);
   if (st.code) return st;
   for (int l = 0; l < s.c.n_blocks; ++l)
@@ -1126,9 +1101,9 @@ Status run_encoder(vla_ctx* c, const void* patches, int n_img, int L, void* out_
   // out_dev may still be the input of the latest prefix
   const bool split = c->encs != c->compute;
   if (split && c->intake_recorded) HIPTRY(hipStreamWaitEvent(c->encs, c->ev_intake, 0));
-  const float* h = ws.h;
+  const float* h = c->ws[VLA_STACK_ENC].h;
   if (s.bf16())
-    PLAUNCH(c, VLA_STACK_ENC, VLA_K_OTHER, vla::f32_to_bf16(h, (bf16_t*)out_dev, n, c->encs, ws.take_parts()));
+    PLAUNCH(c, VLA_STACK_ENC, VLA_K_OTHER, vla::f32_to_bf16(h, (bf16_t*)out_dev, n, c->encs));
   else
     HIPTRY(hipMemcpyAsync(out_dev, h, n * 4, hipMemcpyDeviceToDevice, c->encs));
   if (split) {
@@ -1169,13 +1144,11 @@ Status run_vision(vla_ctx* c, const void* images, int n_img, const void* text, i
     img = v.img;
   }
   const int C = vc.channels, H = vc.img_h, W = vc.img_w, p = vc.patch, m = vc.merge, dh = vc.d_hidden;
-  ws.parts = 0;  // a run that failed part-way may have left some
   if (v.bf16) {
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_STEM, vla::patchify_bf16((const bf16_t*)img, n_img, C, H, W, p, (bf16_t*)v.A,
                                                              v.Kp, v.pos, ws.h, d, st));
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_STEM, vla::gemm_bf16_residual((const bf16_t*)v.A, v.Kp, Stack::packed(v.w_patch, d),
-                                                                  ws.h, d, v.b_patch, M, d, v.Kp, st, 1, ws.part,
-                                                                  split_parts(M, d), &ws.parts));
+                                                                  ws.h, d, v.b_patch, M, d, v.Kp, st));
   } else {
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_STEM, vla::patchify_f32((const float*)img, n_img, C, H, W, p, (float*)v.A, v.Kp,
                                                             v.pos, ws.h, d, st));
@@ -1190,8 +1163,7 @@ Status run_vision(vla_ctx* c, const void* images, int n_img, const void* text, i
   if (split && c->intake_recorded) HIPTRY(hipStreamWaitEvent(st, c->ev_intake, 0));
   if (v.bf16) {
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_CONNECTOR, vla::layernorm_merge_bf16(ws.h, v.post_g, v.post_b, vc.norm_eps,
-                                                                         (bf16_t*)v.merged, n_img, v.gh, v.gw, m, d, st,
-                                                                         ws.take_parts()));
+                                                                         (bf16_t*)v.merged, n_img, v.gh, v.gw, m, d, st));
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_CONNECTOR, vla::gemm_bf16_gelu((const bf16_t*)v.merged, v.md, Stack::packed(v.w_c1, dh),
                                                                    (bf16_t*)v.hid, dh, v.b_c1, nv, dh, v.md, st));
     PLAUNCH(c, VLA_STACK_ENC, VLA_K_CONNECTOR, vla::gemm_bf16_bias((const bf16_t*)v.hid, dh, Stack::packed(v.w_c2, vc.d_out),

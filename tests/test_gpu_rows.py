@@ -1,0 +1,58 @@
+"""A row's result does not depend on which other rows share the call: a
+sequence is bit for bit the same alone, in a batch, and at the head of a longer
+causal call."""
+import numpy as np
+import pytest
+
+import synth
+from paper_2608_14586_amd import binding as vb
+from prefix_cases import EncCase, LlmCase
+
+pytestmark = pytest.mark.gpu
+
+
+def _bits(t):
+    import torch
+    return t.contiguous().view(torch.int16 if t.element_size() == 2 else torch.int32).numpy().copy()
+
+
+def _prefix(ctx, s, dt, tok, k, frame):
+    """(boundary as fp32, KV as bit patterns) of one call over tok[B][L][d]."""
+    B, L = tok.shape[:2]
+    bnd = vb.Boundary(B, L, s.d_model, k, s.n_kv_heads, s.head_dim, stack_dtype=dt, out_dtype="f32")
+    ctx.vla_run_prefix(frame, np.ascontiguousarray(tok), B, L, k, bnd)
+    ctx.vla_wait_boundary(frame, 60000)
+    return bnd.hidden.numpy().copy(), _bits(bnd.kv)
+
+
+# long K with few rows and with many: 7B down (K = 11008), 0.5B down (K = 4864)
+@pytest.mark.parametrize("name,L,B,longer", [("llm7b", 16, 3, 203), ("llm7b", 203, 2, 1000), ("small_llm", 65, 4, 700),
+                                             ("small_llm", 333, 2, 2000)])
+@pytest.mark.parametrize("split", [False, True])
+def test_prefix_rows_alone_and_together(name, L, B, longer, split):
+    c = LlmCase(name, longer, 1, B=B, perturbed=True)
+    if split:
+        c.ctx.vla_set_precision(vb.VLA_STACK_LLM, vb.VLA_PREC_SPLIT)
+    tok = c.tokens(frame=3)
+    hid, kv = _prefix(c.ctx, c.s, "bf16", tok[:, :L], 1, 1)
+    assert np.isfinite(hid).all()
+    for b in range(B):
+        h1, kv1 = _prefix(c.ctx, c.s, "bf16", tok[b:b + 1, :L], 1, 2 + b)
+        assert np.array_equal(h1[0], hid[b]) and np.array_equal(kv1[:, :, 0], kv[:, :, b]), b
+    # whole blocks of 32 queries: the attention rescales by the block's rows
+    n = L // 32 * 32
+    h1, kv1 = _prefix(c.ctx, c.s, "bf16", tok[:1], 1, 9)
+    assert np.array_equal(kv1[:, :, 0, :, :L], kv[:, :, 0])
+    assert np.array_equal(h1[0, :n], hid[0, :n])
+    c.close()
+
+
+@pytest.mark.parametrize("L,n_img", [(100, 3), (257, 6)])
+def test_encoder_images_alone_and_together(L, n_img):
+    c = EncCase("vit_l", n_img, L, n_blocks=2, perturbed=True)
+    p = c.patches(frame=2)
+    whole = c.run(p)
+    c.n_img = 1
+    for i in range(n_img):
+        assert np.array_equal(_bits(c.run(np.ascontiguousarray(p[i:i + 1]))[0]), _bits(whole[i])), i
+    c.close()

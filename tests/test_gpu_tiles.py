@@ -1,5 +1,5 @@
-"""The GEMM's choice of tile and K split over the sizes where it changes, and
-the partial sums a split leaves for the next norm or boundary."""
+"""The GEMM's tiles over the sizes where the choice changes, whole blocks of few
+rows, and several sequences in one call."""
 import numpy as np
 import pytest
 
@@ -50,10 +50,11 @@ def test_products_over_tiles(M, N, K):
 
 @pytest.mark.parametrize("name,L,B", [("small_llm", 1, 1), ("small_llm", 19, 1), ("small_llm", 65, 2),
                                       ("small_llm", 333, 1), ("llm7b", 33, 1), ("llm7b", 203, 1)])
-def test_split_sums_reach_every_reader(name, L, B):
-    """Few rows: the residual products split K.  The boundary (bf16, fp32),
-    the next block's norm and the KV match the oracle, a run in two ranges is
-    bit for bit one run, and a context with room for more rows splits alike."""
+def test_blocks_of_few_rows(name, L, B):
+    """Few rows, where the residual products leave most of the chip idle.  The
+    boundary (bf16, fp32), the next block's norm and the KV match the oracle, a
+    run in two ranges is bit for bit one run, and a context with room for more
+    rows gives the same bits."""
     k = 2 if name == "small_llm" else 1
     c = LlmCase(name, L, k, B=B, perturbed=True)
     tok = c.tokens(frame=4)
@@ -72,7 +73,7 @@ def test_split_sums_reach_every_reader(name, L, B):
 
 
 @pytest.mark.parametrize("n_img,L", [(1, 50), (2, 131), (1, 257)])
-def test_split_sums_in_the_encoder(n_img, L):
+def test_encoder_blocks_of_few_rows(n_img, L):
     c = EncCase("vit_l", n_img, L, n_blocks=2, perturbed=True)
     p = c.patches(frame=2)
     assert rel_l2(to_f32(c.run(p)), c.oracle(p)) <= 1e-2
@@ -108,8 +109,8 @@ def test_fp32_path_odd_shapes(d, H, Hkv, dh, F, L, B):
 
 # Several sequences in one call, of lengths that are not multiples of 16 (or of
 # the quad, or shorter than a group): the V^T groups of a sequence are cut by
-# tiles and by its neighbours.  Products too short to split K, so every row's
-# sums run in one order and each sequence is bit for bit its own call.
+# tiles and by its neighbours.  Every row's sums run in one order in every tile,
+# so each sequence is bit for bit its own call.
 @pytest.mark.parametrize("L,B", [(1, 4), (3, 4), (15, 3), (16, 4), (17, 4), (31, 3), (50, 4), (66, 4), (77, 3),
                                  (130, 4), (333, 2)])
 def test_sequences_side_by_side(L, B):
