@@ -214,7 +214,11 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restr
 #pragma unroll
     for (int d = 0; d < OD; ++d) acc[d] *= alpha;
     __syncthreads();  // sp
-    for (int j = 0; j < AF_K; ++j) {
+    // the sum ends with the query's last key: a weight of zero times a later
+    // token's value is not zero where that value is not finite
+    const int jn = causal ? min(qi - k0 + 1, AF_K) : AF_K;
+#pragma unroll 4
+    for (int j = 0; j < jn; ++j) {
       const float p = sp[qr][j];
 #pragma unroll
       for (int d = 0; d < OD; d += 4) {

@@ -1,12 +1,13 @@
 """A row's result does not depend on which other rows share the call: a
 sequence is bit for bit the same alone, in a batch, and at the head of a longer
-causal call."""
+causal call, whatever the tokens after it hold."""
 import numpy as np
 import pytest
 
 import synth
 from paper_2608_14586_amd import binding as vb
 from prefix_cases import EncCase, LlmCase
+from synth.configs import llama_like
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +57,26 @@ def test_encoder_images_alone_and_together(L, n_img):
     for i in range(n_img):
         assert np.array_equal(_bits(c.run(np.ascontiguousarray(p[i:i + 1]))[0]), _bits(whole[i])), i
     c.close()
+
+
+def _stack(s, dt, L, B, name):
+    wl = synth.Workload(name, dt, s, None, batch=B, seq=L)
+    ctx = vb.Context(llm=vb.stack_cfg(s, dt, max_tokens=L, max_batch=B))
+    for l in range(s.n_blocks):
+        ctx.vla_load_block_weights(vb.VLA_STACK_LLM, l, synth.llm_block_weights(wl, l, perturbed=True))
+    return ctx, synth.tokens(wl, frame=1)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("j", [1, 16, 63, 64, 100, 129])
+def test_fp32_tokens_before_one_that_is_not_finite(j, bad):
+    """Causality also for what a later token poisons: the rows before it keep
+    their bits, whatever key tile and query block they share with it."""
+    s = llama_like(2, 256, 4, 2, 64, 688)
+    ctx, tok = _stack(s, "f32", 130, 1, "rows_nan")
+    hid, kv = _prefix(ctx, s, "f32", tok, 2, 1)
+    tok[0, j, 5] = bad
+    h1, kv1 = _prefix(ctx, s, "f32", tok, 2, 2)
+    assert np.array_equal(h1[0, :j], hid[0, :j]) and np.array_equal(kv1[:, :, 0, :, :j], kv[:, :, 0, :, :j])
+    assert not np.isfinite(h1[0, j:]).any()
+    ctx.vla_destroy()
