@@ -17,7 +17,9 @@ namespace {
 // SPLIT: the four waves take a quarter of K each of one 32x32 tile and add
 // their sums in LDS, so that a product of few tiles still fills the chip and
 // its chain of loads is a quarter as long; otherwise they take the four
-// quadrants of a 64x64 tile.  A 128-row product of the d=256 stack (K = 256
+// quadrants of a 64x64 tile.  Both sum the quarters on their own and add them
+// in the same order, so that a row's bits do not depend on how many rows share
+// the call.  A 128-row product of the d=256 stack (K = 256
 // and 688) took 57 us with 64x64 VALU tiles in 16-deep LDS slabs (8 to 24
 // workgroups, two barriers a slab) and takes 8.
 // VEC: rows are 16-byte aligned; otherwise elements load one by one.
@@ -35,8 +37,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   const float* ar = A + (size_t)min(m0 + li, M - 1) * lda + 4 * half;
   const float* wr = W + (size_t)min(n0 + li, N - 1) * ldw + 4 * half;
   const int steps = (K + 7) / 8;
-  const int s0 = SPLIT ? steps * wave / 4 : 0, s1 = SPLIT ? steps * (wave + 1) / 4 : steps;
-  f32x16 acc = {};
   auto load = [&](const float* r, int s) {
     const int k = s * 8;
     if (VEC && k + 8 <= K) return *(const f32x4*)(r + k);
@@ -46,22 +46,28 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       if (k + 4 * half + j < K) v[j] = r[k + j];
     return v;
   };
-  constexpr int U = 8;
-  int s = s0;
-  for (; s + U <= s1; s += U) {
-    f32x4 a[U], w[U];
+  // the sum over quarter q of K
+  auto quarter = [&](int q) {
+    constexpr int U = 8;
+    const int s1 = steps * (q + 1) / 4;
+    int s = steps * q / 4;
+    f32x16 acc = {};
+    for (; s + U <= s1; s += U) {
+      f32x4 a[U], w[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = load(ar, s + u), w[u] = load(wr, s + u);
+      for (int u = 0; u < U; ++u) a[u] = load(ar, s + u), w[u] = load(wr, s + u);
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][j], w[u][j], acc, 0, 0, 0);
-  }
-  for (; s < s1; ++s) {
-    const f32x4 a = load(ar, s), w = load(wr, s);
+        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][j], w[u][j], acc, 0, 0, 0);
+    }
+    for (; s < s1; ++s) {
+      const f32x4 a = load(ar, s), w = load(wr, s);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], w[j], acc, 0, 0, 0);
-  }
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], w[j], acc, 0, 0, 0);
+    }
+    return acc;
+  };
   const int col = n0 + li;
   const float bv = bias && col < N ? bias[col] : 0.f;
   auto store = [&](int r, float v) {
@@ -72,6 +78,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     *p = mode == 1 ? *p + v : v;
   };
   if constexpr (SPLIT) {
+    const f32x16 acc = quarter(wave);
 #pragma unroll
     for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
     __syncthreads();
@@ -81,8 +88,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       store(r, (red[0][r][lane] + red[1][r][lane]) + (red[2][r][lane] + red[3][r][lane]));
     }
   } else {
+    f32x16 sum = {};
+#pragma unroll 1
+    for (int p = 0; p < 4; p += 2) {
+      const f32x16 a = quarter(p), b = quarter(p + 1);
+      sum = p ? sum + (a + b) : a + b;
+    }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) store(r, acc[r]);
+    for (int r = 0; r < 16; ++r) store(r, sum[r]);
   }
 }
 

@@ -67,6 +67,18 @@ def _stack(s, dt, L, B, name):
     return ctx, synth.tokens(wl, frame=1)
 
 
+# gate/up of 8200 columns: under and over 256 tiles of 64x64
+def test_fp32_rows_alone_and_together():
+    s = llama_like(1, 512, 8, 2, 64, 4100)
+    ctx, tok = _stack(s, "f32", 64, 4, "rows_f32")
+    hid, kv = _prefix(ctx, s, "f32", tok, 1, 1)
+    assert np.isfinite(hid).all()
+    for b in range(4):
+        h1, kv1 = _prefix(ctx, s, "f32", tok[b:b + 1], 1, 2 + b)
+        assert np.array_equal(h1[0], hid[b]) and np.array_equal(kv1[:, :, 0], kv[:, :, b]), b
+    ctx.vla_destroy()
+
+
 @pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
 @pytest.mark.parametrize("j", [1, 16, 63, 64, 100, 129])
 def test_fp32_tokens_before_one_that_is_not_finite(j, bad):
