@@ -290,7 +290,11 @@ struct StageCopy {
 // partials part[B][H][ns][2 + dh] that attn_decode_kernel wrote (see
 // combine_kernel, whose launch this saves): every workgroup reads all of
 // them, so it is for few heads and splits (decode_oproj).  The weight of each
-// (row, head, split), 2^(m_s - m) / sum, goes to LDS first.
+// (row, head, split), the factor of each batch of CB splits and the sum of
+// each (row, head) go to LDS first.  Every product and sum is combine_kernel's,
+// in its order, so that a step's bits do not depend on which of the two ran
+// (a batch takes the launch where one sequence does not).
+constexpr int CB = 16;        // splits per batch of the combination
 constexpr int SC_MAX = 1024;  // weights that fit
 struct StageCombine {
   const float* part;
@@ -305,13 +309,14 @@ struct StageCombine {
   template <int NB>
   __device__ __forceinline__ void prepare_pre(const Pre<NB>&, float*, int, int, int, float*) const {}
   static __device__ __forceinline__ float* weights() {
-    __shared__ float w[2 * SC_MAX];
+    __shared__ float w[3 * SC_MAX];
     return w;
   }
   // one (row, head, split) per thread: its maximum and sum to LDS, then its
-  // weight from its head's
+  // weight against the maximum up to its batch, and with the batch's first
+  // split the factor of what the batches before it summed; then the sums
   __device__ void prepare(float*, int B, int, int tid, float*) const {
-    float *w = weights(), *ml = w + SC_MAX;
+    float *w = weights(), *ml = w + SC_MAX, *rb = ml + SC_MAX;
     const int n = B * H * ns, stride = 2 + dh;
     for (int i = tid; i < n; i += 256) {
       w[i] = part[(size_t)i * stride];
@@ -323,11 +328,13 @@ struct StageCombine {
     for (int u = 0; u < SC_MAX / 256; ++u) {
       const int i = tid + 256 * u;
       if (i < n) {
-        const int i0 = i / ns * ns;
-        float m = -INFINITY, l = 0.f;
-        for (int s = 0; s < ns; ++s) m = fmaxf(m, w[i0 + s]);
-        for (int s = 0; s < ns; ++s) l += (w[i0 + s] == -INFINITY ? 0.f : exp2f(w[i0 + s] - m)) * ml[i0 + s];
-        wt[u] = (w[i] == -INFINITY ? 0.f : exp2f(w[i] - m)) / l;
+        const int i0 = i / ns * ns, c0 = (i - i0) / CB * CB, c1 = min(c0 + CB, ns);
+        float m = -INFINITY;
+        for (int s = 0; s < c0; ++s) m = fmaxf(m, w[i0 + s]);
+        float mn = m;
+        for (int s = c0; s < c1; ++s) mn = fmaxf(mn, w[i0 + s]);
+        if (i == i0 + c0) rb[i] = m == -INFINITY ? 0.f : exp2f(m - mn);
+        wt[u] = w[i] == -INFINITY ? 0.f : exp2f(w[i] - mn);
       }
     }
     __syncthreads();
@@ -335,12 +342,23 @@ struct StageCombine {
     for (int u = 0; u < SC_MAX / 256; ++u)
       if (tid + 256 * u < n) w[tid + 256 * u] = wt[u];
     __syncthreads();
+    for (int i = tid; i < B * H; i += 256) {
+      const int i0 = i * ns;
+      float l = 0.f;
+      for (int s = 0; s < ns; ++s) {
+        const float x = ml[i0 + s];
+        l = s % CB ? fmaf(w[i0 + s], x, l) : fmaf(l, rb[i0 + s], w[i0 + s] * x);
+      }
+      ml[i0] = l;
+    }
+    __syncthreads();
   }
   // columns i..i+3 of row b (one head: dh % 4 == 0); the loads of eight
   // splits are in flight together, past the last they repeat it with weight 0
   __device__ __forceinline__ u32x2 at4(int b, int i) const {
     const int h = i / dh, d = i - h * dh, stride = 2 + dh;
     const float* w = weights() + (b * H + h) * ns;
+    const float* rb = w + 2 * SC_MAX;
     const float* p = part + (size_t)(b * H + h) * ns * stride + 2 + d;
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     float x[4] = {0.f, 0.f, 0.f, 0.f};
@@ -354,12 +372,18 @@ struct StageCombine {
         v[s][1] = *(const f32x2*)(p + si * stride + 2);
         ws[s] = s0 + s < ns ? w[si] : 0.f;
       }
+      const bool head = s0 % CB == 0;
+      const float r = head ? rb[s0] : 0.f;
 #pragma unroll
       for (int s = 0; s < 8; ++s)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = fmaf(ws[s], v[s][e / 2][e % 2], x[e]);
+        for (int e = 0; e < 4; ++e) {
+          const float o = v[s][e / 2][e % 2];
+          x[e] = s == 0 && head ? fmaf(x[e], r, ws[s] * o) : fmaf(ws[s], o, x[e]);
+        }
     }
-    return u32x2{pack_bf2(x[0], x[1]), pack_bf2(x[2], x[3])};
+    const float l = w[SC_MAX];
+    return u32x2{pack_bf2(x[0] / l, x[1] / l), pack_bf2(x[2] / l, x[3] / l)};
   }
   __device__ void fill(bf16_t* xs, const float*, int Bp, int, int, int k0, int n, int tid) const {
     for (int b = 0; b < Bp; ++b)
@@ -905,11 +929,12 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const float* __restric
 // (b, h), one thread per dimension.  Every split's values are loaded before
 // any is combined, without branches (indices past the last split repeat it
 // and get weight zero): per-element branches around the loads made the
-// compiler wait for each load in turn.
+// compiler wait for each load in turn.  The products and sums are spelled out
+// (StageCombine forms the same).
 template <int DH>
 __global__ __launch_bounds__(DH) void combine_kernel(const float* __restrict__ part, int nsplit,
                                                      bf16_t* __restrict__ o) {
-  constexpr int MAXS = 16;
+  constexpr int MAXS = CB;
   const int bh = blockIdx.x, d = threadIdx.x, stride = 2 + DH;
   const float* p = part + (size_t)bh * nsplit * stride;
   float m = -INFINITY, l = 0.f, acc = 0.f;
@@ -929,13 +954,11 @@ __global__ __launch_bounds__(DH) void combine_kernel(const float* __restrict__ p
 #pragma unroll
     for (int s = 0; s < MAXS; ++s) mn = fmaxf(mn, ms[s]);
     const float r = m == -INFINITY ? 0.f : exp2f(m - mn);
-    l *= r;
-    acc *= r;
 #pragma unroll
     for (int s = 0; s < MAXS; ++s) {
       const float w = ms[s] == -INFINITY ? 0.f : exp2f(ms[s] - mn);
-      l += w * ls[s];
-      acc += w * os[s];
+      l = s ? fmaf(w, ls[s], l) : fmaf(l, r, w * ls[s]);
+      acc = s ? fmaf(w, os[s], acc) : fmaf(acc, r, w * os[s]);
     }
     m = mn;
   }

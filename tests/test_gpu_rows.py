@@ -1,6 +1,7 @@
 """A row's result does not depend on which other rows share the call: a
 sequence is bit for bit the same alone, in a batch, and at the head of a longer
-causal call, whatever the tokens after it hold."""
+causal call, whatever the tokens after it hold; in a prefix, in the encoder and
+in a decode step."""
 import numpy as np
 import pytest
 
@@ -91,4 +92,36 @@ def test_fp32_tokens_before_one_that_is_not_finite(j, bad):
     h1, kv1 = _prefix(ctx, s, "f32", tok, 2, 2)
     assert np.array_equal(h1[0, :j], hid[0, :j]) and np.array_equal(kv1[:, :, 0, :, :j], kv[:, :, 0, :, :j])
     assert not np.isfinite(h1[0, j:]).any()
+    ctx.vla_destroy()
+
+
+# the O-projection combines the split-key partials for one sequence and a
+# launch of its own does for four: one split, a few, past 16; many tokens, as
+# a last bit of the combined value shows only where its bf16 rounds the other way
+TOKENS = 24
+@pytest.mark.parametrize("pos", [100, 1500, 2048, 2600, 4100])
+def test_decode_rows_alone_and_together(pos):
+    import torch
+    s = llama_like(1, 896, 14, 2, 64, 512)
+    B, L_cap = 4, pos + 5
+    ctx, _ = _stack(s, "bf16", L_cap, B, "rows_decode")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(pos)
+    cache = torch.empty((1, 2, B, 2, L_cap, 64), dtype=torch.bfloat16, device="cuda").normal_(0.0, 1.0, generator=gen)
+    x = synth.normal_bf16(synth.seed_of("rows_decode_x", pos), (TOKENS, B, 896))
+
+    def step(t, frame, rows):
+        n = len(rows)
+        c = cache[:, :, rows].contiguous()
+        torch.cuda.synchronize()  # written on torch's stream, read on the context's
+        ob = vb.Boundary(n, 1, 896, 0, 2, 64, out_dtype="f32", with_kv=False)
+        ctx.vla_decode_step(frame, np.ascontiguousarray(x[t, rows]), n, pos, 1, c, L_cap, ob)
+        ctx.vla_wait_boundary(frame, 60000)
+        return ob.hidden.numpy().reshape(n, -1).copy()
+
+    for t in range(TOKENS):
+        whole = step(t, 8 * t, list(range(B)))
+        assert np.isfinite(whole).all()
+        for b in range(B):
+            assert np.array_equal(step(t, 8 * t + 1 + b, [b])[0], whole[b]), (t, b)
     ctx.vla_destroy()
