@@ -58,6 +58,7 @@ namespace {
 constexpr int GV_KCH = 2048;       // K elements staged per chunk
 constexpr int GV_MB = 4;           // largest batch
 constexpr int ATT_KC = 128;        // keys per attention split
+constexpr int GS_KC = 1024;        // k per chunk of the streaming kernel: 16 slabs, 4 per wave
 
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -128,6 +129,16 @@ struct StageNorm {
 #pragma unroll
     for (int j = 0; j < PRE; ++j) r.g[j] = __builtin_bit_cast(f32x4, buffer_load16(rg, (tid + 256 * j) * 16));
   }
+  // what bf16(y) leaves out of y = x * g (rounded to bf16 by the caller): of
+  // the rounded product, as fill_row takes it, and for rows shorter than a
+  // chunk of the exact one, as the chunked kernel's fill does (a fused
+  // multiply-subtract).  Which one shows in the last bit of the remainder; a
+  // row's is the same whether its loads were early or not.
+  static __device__ __forceinline__ float remainder(float x, float g, float y, int K) {
+#pragma clang fp contract(off)
+    const float hi = bf2f(f2bf(y));
+    return K < GS_KC ? fmaf(x, g, -hi) : y - hi;
+  }
   // staged rows from the preloaded registers
   template <int NB, int P>
   __device__ __forceinline__ void fill_pre(const Pre<NB>& r, bf16_t* xs, int Kp, const float* sc, int B, int K,
@@ -140,15 +151,15 @@ struct StageNorm {
       for (int j = 0; j < PRE; ++j) {
         const int i = (tid + 256 * j) * 4;
         if (i >= K) break;
-        f32x4 y;
+        f32x4 y, lo;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = r.h[b][j][e] * s * r.g[j][e];
-        *(u32x2*)(xs + (size_t)(b * P) * Kp + i) = u32x2{pack_bf2(y[0], y[1]), pack_bf2(y[2], y[3])};
-        if constexpr (P == 2) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = lo_part(y[e]);
-          *(u32x2*)(xs + (size_t)(b * P + 1) * Kp + i) = u32x2{pack_bf2(y[0], y[1]), pack_bf2(y[2], y[3])};
+        for (int e = 0; e < 4; ++e) {
+          y[e] = r.h[b][j][e] * s * r.g[j][e];
+          if constexpr (P == 2) lo[e] = remainder(r.h[b][j][e] * s, r.g[j][e], y[e], K);
         }
+        *(u32x2*)(xs + (size_t)(b * P) * Kp + i) = u32x2{pack_bf2(y[0], y[1]), pack_bf2(y[2], y[3])};
+        if constexpr (P == 2)
+          *(u32x2*)(xs + (size_t)(b * P + 1) * Kp + i) = u32x2{pack_bf2(lo[0], lo[1]), pack_bf2(lo[2], lo[3])};
       }
     }
   }
@@ -529,8 +540,6 @@ __global__ __launch_bounds__(256) void gemv_chunk_kernel(Stage sg, const bf16_t*
     }
   }
 }
-
-constexpr int GS_KC = 1024;  // k per chunk of the streaming kernel: 16 slabs, 4 per wave
 
 // k per chunk: the paired kernel, twice the rows per lane, keeps the same
 // bytes in flight

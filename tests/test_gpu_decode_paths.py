@@ -5,6 +5,7 @@ kernel or copied."""
 import numpy as np
 import pytest
 
+import synth
 from paper_2608_14586_amd import binding as vb
 from prefix_cases import rel_l2
 from synth.configs import llama_like
@@ -61,4 +62,54 @@ def test_decode_boundary_at_any_alignment():
             got.append(buf[at:at + B * 512].clone())
             assert not buf[at + B * 512:].any()
         assert got[0].any() and torch.equal(got[0], got[1])
+    ctx.vla_destroy()
+
+
+# widths the chunked products took before the streaming ones staged their rows
+# early, and widths above one chunk: each has its own form of the remainder
+@pytest.mark.parametrize("d,B", [(512, 1), (896, 3), (1024, 1), (4096, 1), (4096, 3)])
+def test_split_operands_to_the_last_bit(d, B):
+    """hi = bf16(v), lo = bf16(v - hi) of the normalised row, bit for bit.  With
+    w_o = 0, one gate feature for all and unit up and down rows the boundary is
+    x + G (hi + lo), every step of it exact or one fp32 rounding."""
+    import torch
+    F = d
+    s = llama_like(1, d, 1, 1, 64, F)
+    wl = synth.Workload("split_bits_%d" % d, "bf16", s, None)
+    W = synth.llm_block_weights(wl, 0, perturbed=True)
+    one, gate = np.uint16(0x3F80), np.uint16(0x4280)  # 1, 64
+    W["w_o"] = np.zeros_like(W["w_o"])
+    W["w_gate"], W["w_up"], W["w_down"] = (np.zeros_like(W[n]) for n in ("w_gate", "w_up", "w_down"))
+    W["w_gate"][:, 0] = gate
+    W["w_up"][np.arange(F), np.arange(F)] = one
+    W["w_down"][np.arange(d), np.arange(F)] = one
+    ctx = vb.Context(llm=vb.stack_cfg(s, "bf16", max_tokens=64, max_batch=B))
+    ctx.vla_load_block_weights(vb.VLA_STACK_LLM, 0, W)
+    ctx.vla_set_precision(vb.VLA_STACK_LLM, vb.VLA_PREC_SPLIT)
+    rng = np.random.default_rng(d + B)
+    x = rng.integers(1, 16, (B, d)) * rng.choice([-1, 1], (B, d))  # sums of their squares are exact
+    x[:, 0] = 15
+    cache = torch.zeros((1, 2, B, 1, 8, 64), dtype=torch.bfloat16, device="cuda")
+    torch.cuda.synchronize()
+    ob = vb.Boundary(B, 1, d, 0, 1, 64, out_dtype="f32", with_kv=False)
+    x16 = torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16)
+    ctx.vla_decode_step(1, x16.view(torch.int16).numpy().view(np.uint16), B, 0, 1, cache, 8, ob)
+    ctx.vla_wait_boundary(1, 60000)
+
+    def bf(a):
+        return torch.from_numpy(np.asarray(a, np.float32)).to(torch.bfloat16).to(torch.float32).numpy()
+
+    f = np.float32
+    ms = (x * x).sum(1).astype(f) / f(d) + f(s.norm_eps)
+    hs = x.astype(f) * (f(1) / np.sqrt(ms))[:, None]
+    g = synth.as_f32(W["norm2_g"])
+    y = hs * g
+    hi = bf(y)
+    exact = (hs.astype(np.float64) * g - hi).astype(f)
+    u = hi + bf(exact if d < 1024 else y - hi)
+    a = (u[:, :1] * f(64)) * u
+    ahi = bf(a)
+    want = x.astype(f) + (ahi + bf(a - ahi))
+    got = ob.hidden.numpy().reshape(B, d)
+    assert np.array_equal(got, want), (np.argwhere(got != want)[:5], (got != want).sum())
     ctx.vla_destroy()
