@@ -187,6 +187,7 @@ struct Slot {
   uint64_t frame_id = 0;
   bool used = false;
   bool has_kv = false;
+  bool decode = false;  // a decode step
   bool direct = false;  // the boundary was stored to the host by a kernel (decode steps)
   void* kv = nullptr;   // device [n_blocks][2][B][Hkv][L][dh]
   void* hid = nullptr;  // device staging of the boundary
@@ -886,7 +887,7 @@ Status run_blocks(vla_ctx* c, uint64_t frame_id, const void* tokens, vla_dtype i
   c->history.erase(frame_id);
   sl.frame_id = frame_id;
   sl.used = true;
-  sl.direct = false;
+  sl.decode = sl.direct = false;
   out->frame_id = frame_id;
   st = enqueue_blocks(c, sl, tokens, in_dt, B, L, k0, k1, out);
   return st.code ? abandon_frame(c, sl, st) : OK;
@@ -1006,6 +1007,7 @@ Status decode_step(vla_ctx* c, uint64_t frame_id, const void* x, int B, int pos,
   c->history.erase(frame_id);
   sl.frame_id = frame_id;
   sl.used = true;
+  sl.decode = true;
   sl.direct = false;
   out->frame_id = frame_id;
   if (!buf.hid) buf.hid = sl.hid;
@@ -1503,10 +1505,11 @@ vla_status vla_wait_boundary(vla_ctx* ctx, uint64_t frame_id, int timeout_ms) {
             return finish(ctx, fail(VLA_ERR_TIMEOUT, "frame %llu not done after %d ms", (unsigned long long)frame_id,
                                     timeout_ms));
         }
-        // The first 2 ms are polled: a sleep, 20 us asked and 70-80 slept, is
-        // much of a decode step (two 7B blocks: 200 us of kernels); longer
-        // waits, a prefix frame's, leave the core to others.
-        if (std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(2))
+        // A decode step is polled for its first 2 ms: a sleep, 20 us asked
+        // and 70-80 slept, is much of one (two 7B blocks: 200 us of kernels).
+        // Waits for a prefix frame leave the core to others, the host suffix
+        // among them, as do longer ones.
+        if (sl.decode && std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(2))
           std::this_thread::yield();
         else
           std::this_thread::sleep_for(std::chrono::microseconds(20));

@@ -113,3 +113,25 @@ def test_split_operands_to_the_last_bit(d, B):
     got = ob.hidden.numpy().reshape(B, d)
     assert np.array_equal(got, want), (np.argwhere(got != want)[:5], (got != want).sum())
     ctx.vla_destroy()
+
+
+def test_waiting_for_a_prefix_leaves_the_core():
+    """The wait for a prefix frame sleeps; only a decode step's is polled."""
+    import time
+
+    import torch
+    from prefix_cases import LlmCase
+    c = LlmCase("llm7b", 2048, 1, perturbed=True)
+    tok = c.tokens()
+    dev = torch.from_numpy(tok.view(np.int16)).cuda()
+    bnd = c.boundary()
+    cpu = wall = 0.0
+    for f in range(24):
+        c.ctx.vla_run_prefix(f, dev, 1, 2048, 1, bnd)
+        t, w = time.thread_time(), time.perf_counter()
+        c.ctx.vla_wait_boundary(f, 60000)
+        if f >= 4:
+            cpu, wall = cpu + time.thread_time() - t, wall + time.perf_counter() - w
+    # about 0.9 ms a frame in sleeps of 70-80 us, each followed by one query
+    assert cpu < 0.5 * wall, (cpu, wall)
+    c.close()
