@@ -164,8 +164,8 @@ hipError_t layernorm_merge_f32(const float* x, const float* g, const float* b, f
                                int gh, int gw, int m, int d, hipStream_t s);
 hipError_t bf16_to_f32(const bf16_t* x, float* y, size_t n, hipStream_t s);
 hipError_t f32_to_bf16(const float* x, bf16_t* y, size_t n, hipStream_t s);
-// y = x, fp32, by a kernel (y may be pinned host memory)
-hipError_t f32_store(const float* x, float* y, size_t n, hipStream_t s);
+// y = x, by a kernel (y may be pinned host memory): whole 16-byte words, up to 16 MB
+hipError_t copy16(const void* x, void* y, size_t bytes, hipStream_t s);
 
 // ------------------------------------------------------------- fp32 debug path
 // C[M][N] (op) A[M][K] * W[N][K]^T in fp32 FMA; mode 0: C = acc + bias,

@@ -153,27 +153,23 @@ __global__ void bf16_to_f32_kernel(const bf16_t* __restrict__ x, float* __restri
   }
 }
 
-// y = x, as bf16 or fp32
-template <class OutT>
-__global__ void f32_store_kernel(const float* __restrict__ x, OutT* __restrict__ y, size_t n) {
+__global__ void f32_to_bf16_kernel(const float* __restrict__ x, bf16_t* __restrict__ y, size_t n) {
   size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 8;
   size_t stride = (size_t)gridDim.x * blockDim.x * 8;
   for (; i < n; i += stride) {
     if (i + 8 <= n) {
       f32x4 a = *(const f32x4*)(x + i), b = *(const f32x4*)(x + i + 4);
-      if constexpr (sizeof(OutT) == 2) {
-        *(u32x4*)(y + i) = u32x4{pack_bf2(a[0], a[1]), pack_bf2(a[2], a[3]), pack_bf2(b[0], b[1]), pack_bf2(b[2], b[3])};
-      } else {
-        *(f32x4*)(y + i) = a;
-        *(f32x4*)(y + i + 4) = b;
-      }
+      u32x4 w = {pack_bf2(a[0], a[1]), pack_bf2(a[2], a[3]), pack_bf2(b[0], b[1]), pack_bf2(b[2], b[3])};
+      *(u32x4*)(y + i) = w;
     } else {
-      for (size_t j = i; j < n; ++j) {
-        if constexpr (sizeof(OutT) == 2) y[j] = f2bf(x[j]);
-        else y[j] = x[j];
-      }
+      for (size_t j = i; j < n; ++j) y[j] = f2bf(x[j]);
     }
   }
+}
+
+__global__ void copy16_kernel(const u32x4* __restrict__ x, u32x4* __restrict__ y, size_t n) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) y[i] = x[i];
 }
 
 inline unsigned ew_grid(size_t n) {
@@ -220,13 +216,15 @@ hipError_t bf16_to_f32(const bf16_t* x, float* y, size_t n, hipStream_t s) {
 
 hipError_t f32_to_bf16(const float* x, bf16_t* y, size_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL((f32_store_kernel<bf16_t>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n);
+  hipLaunchKernelGGL(f32_to_bf16_kernel, dim3(ew_grid(n)), dim3(256), 0, s, x, y, n);
   return hipGetLastError();
 }
 
-hipError_t f32_store(const float* x, float* y, size_t n, hipStream_t s) {
+hipError_t copy16(const void* x, void* y, size_t bytes, hipStream_t s) {
+  const size_t n = bytes / 16;
+  if (bytes % 16 || (uintptr_t)x % 16 || (uintptr_t)y % 16 || n > (size_t)1 << 20) return hipErrorInvalidValue;
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL((f32_store_kernel<float>), dim3(ew_grid(n)), dim3(256), 0, s, x, y, n);
+  hipLaunchKernelGGL(copy16_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const u32x4*)x, (u32x4*)y, n);
   return hipGetLastError();
 }
 

@@ -188,7 +188,6 @@ struct Slot {
   bool used = false;
   bool has_kv = false;
   bool decode = false;  // a decode step
-  bool direct = false;  // the boundary was stored to the host by a kernel (decode steps)
   void* kv = nullptr;   // device [n_blocks][2][B][Hkv][L][dh]
   void* hid = nullptr;  // device staging of the boundary
   hipEvent_t ev_start = nullptr, ev_done = nullptr, ev_hid = nullptr, ev_copied = nullptr;
@@ -564,14 +563,19 @@ bool is_pinned_host(const void* p) {
   return a.type == hipMemoryTypeHost;
 }
 
-// The address kernels write pinned host memory at, NULL if there is none or
-// it is not aligned for 16-byte stores.
-void* kernel_ptr(const void* p) {
+// The address kernels on `device` write pinned host memory at.  NULL where
+// that is in doubt: no such address, none aligned for 16-byte stores, memory
+// allocated for another device only, or not known to be coherent (the host's
+// view then depends on how an event releases it).
+void* kernel_ptr(void* p, int device) {
   hipPointerAttribute_t a;
-  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+  unsigned flags = 0;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || hipHostGetFlags(&flags, p) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
+  constexpr unsigned known = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent | hipHostMallocNumaUser;
+  if ((flags & ~known) || (a.device != device && !(flags & hipHostMallocPortable))) return nullptr;
   return (uintptr_t)a.devicePointer % 16 ? nullptr : a.devicePointer;
 }
 
@@ -797,7 +801,7 @@ Status retire_slot(vla_ctx* c, Slot& sl) {
   HIPTRY(hipEventSynchronize(sl.ev_copied));
   FrameTimes t{};
   HIPTRY(hipEventElapsedTime(&t.gpu, sl.ev_start, sl.ev_done));
-  HIPTRY(hipEventElapsedTime(&t.xfer, sl.direct ? sl.ev_done : sl.ev_hid, sl.ev_copied));
+  HIPTRY(hipEventElapsedTime(&t.xfer, sl.ev_hid, sl.ev_copied));
   HIPTRY(hipEventElapsedTime(&t.total, sl.ev_start, sl.ev_copied));
   c->history.put(sl.frame_id, t);
   sl.used = false;
@@ -887,7 +891,7 @@ Status run_blocks(vla_ctx* c, uint64_t frame_id, const void* tokens, vla_dtype i
   c->history.erase(frame_id);
   sl.frame_id = frame_id;
   sl.used = true;
-  sl.decode = sl.direct = false;
+  sl.decode = false;
   out->frame_id = frame_id;
   st = enqueue_blocks(c, sl, tokens, in_dt, B, L, k0, k1, out);
   return st.code ? abandon_frame(c, sl, st) : OK;
@@ -1008,7 +1012,6 @@ Status decode_step(vla_ctx* c, uint64_t frame_id, const void* x, int B, int pos,
   sl.frame_id = frame_id;
   sl.used = true;
   sl.decode = true;
-  sl.direct = false;
   out->frame_id = frame_id;
   if (!buf.hid) buf.hid = sl.hid;
   st = enqueue_decode(c, sl, x, B, pos, k, kv_cache, L_cap, out, buf, fixed);
@@ -1056,22 +1059,6 @@ Status enqueue_decode(vla_ctx* c, Slot& sl, const void* x, int B, int pos, int k
     PLAUNCH(c, VLA_STACK_LLM, VLA_K_MLP_UP, vla::decode_up(h, w.n2g, cf.norm_eps, Stack::packed(w.w_up, 2 * s.f_pad), s.f_pad, gu, abuf, B, d, cs, P));
     PLAUNCH(c, VLA_STACK_LLM, VLA_K_MLP_DOWN, vla::decode_down(abuf, s.f_pad, Stack::packed(w.w_down, d), h, B, d, cs, P));
   }
-  // The boundary is a few KB: the cast stores it in the pinned buffer itself,
-  // which saves the copy stream's wait and its copy (0.5B-shaped step, 12
-  // blocks: about 10 us of 490).  ev_done precedes the store, so T_X is the
-  // store's time.
-  if (void* host = kernel_ptr(out->hidden)) {
-    sl.direct = true;
-    HIPTRY(hipEventRecord(sl.ev_done, cs));
-    if (out->out_dtype == VLA_BF16)
-      PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_to_bf16(h, (bf16_t*)host, n, cs));
-    else
-      PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_store(h, (float*)host, n, cs));
-    HIPTRY(hipEventRecord(sl.ev_copied, cs));
-    // whoever orders itself after the copy stream still follows the handoff
-    HIPTRY(hipStreamWaitEvent(c->copy, sl.ev_copied, 0));
-    return OK;
-  }
   if (out->out_dtype == VLA_BF16)
     PLAUNCH(c, VLA_STACK_LLM, VLA_K_OTHER, vla::f32_to_bf16(h, (bf16_t*)buf.hid, n, cs));
   else
@@ -1079,7 +1066,14 @@ Status enqueue_decode(vla_ctx* c, Slot& sl, const void* x, int B, int pos, int k
   HIPTRY(hipEventRecord(sl.ev_done, cs));
   HIPTRY(hipStreamWaitEvent(c->copy, sl.ev_done, 0));
   HIPTRY(hipEventRecord(sl.ev_hid, c->copy));
-  HIPTRY(copy_d2h(out->hidden, buf.hid, hid_bytes, c->copy));
+  // A few KB: stored by a kernel on the copy stream where that can be done, 7
+  // us less than a DMA copy (7B-shaped step, two blocks: 233 and 240 us).
+  // (Stored by the cast itself, on the compute stream, the step took 222, but
+  // then the handoff overtook what the caller had queued on the copy stream.)
+  if (void* host = hid_bytes % 16 ? nullptr : kernel_ptr(out->hidden, c->device))
+    HIPTRY(vla::copy16(buf.hid, host, hid_bytes, c->copy));
+  else
+    HIPTRY(copy_d2h(out->hidden, buf.hid, hid_bytes, c->copy));
   HIPTRY(hipEventRecord(sl.ev_copied, c->copy));
   return OK;
 }

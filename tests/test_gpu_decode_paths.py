@@ -1,7 +1,7 @@
 """The decode step's routes by size: streaming and chunked products, preloaded
 input rows, one and several sequences, the split-key partials combined in a
 launch of their own or in the O-projection, and the boundary stored by a
-kernel or copied."""
+kernel or copied, on the copy stream."""
 import numpy as np
 import pytest
 
@@ -135,3 +135,62 @@ def test_waiting_for_a_prefix_leaves_the_core():
     # about 0.9 ms a frame in sleeps of 70-80 us, each followed by one query
     assert cpu < 0.5 * wall, (cpu, wall)
     c.close()
+
+
+def _step(ctx, frame, x, B, pos, cache, hidden, dt="f32"):
+    """One decode step whose boundary goes to the pinned address `hidden`."""
+    ob = vb.Boundary(B, 1, x.shape[-1], 0, 2, 128, out_dtype=dt, with_kv=False)
+    ob.c.hidden = hidden
+    ctx.vla_decode_step(frame, np.ascontiguousarray(x), B, pos, 1, cache, cache.shape[4], ob)
+
+
+def test_decode_boundary_follows_the_copy_stream():
+    """A read of the boundary buffer that the caller has queued on the copy
+    stream comes before the next step's handoff into that buffer."""
+    import torch
+    shape = llama_like(1, 512, 4, 2, 128, 512)
+    B, L = 2, 20
+    _, _, toks, _, cache, ctx = _run(shape, B, L, 1, 2, "route_order")
+    copy = ctx.copy_stream
+    hidden = torch.zeros(B * 512, dtype=torch.float32, pin_memory=True)
+    big = torch.zeros(1 << 28, dtype=torch.int32, device="cuda")
+    got = torch.empty(B * 512, dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    _step(ctx, 60, toks[:, L], B, L, cache, hidden.data_ptr())
+    ctx.vla_wait_boundary(60, 60000)
+    first = hidden.clone()
+    with torch.cuda.stream(copy):
+        for _ in range(20):  # milliseconds of earlier work on the copy stream
+            big.add_(1)
+        got.copy_(hidden, non_blocking=True)
+    _step(ctx, 61, toks[:, L + 1], B, L + 1, cache, hidden.data_ptr())
+    ctx.vla_wait_boundary(61, 60000)
+    torch.cuda.synchronize()
+    assert not torch.equal(hidden, first)
+    assert torch.equal(got.cpu(), first)
+    ctx.vla_destroy()
+
+
+def test_decode_boundary_into_any_pinned_memory():
+    """Into the middle of an allocation and into non-coherent host memory: the
+    same bytes, and none around them."""
+    import ctypes
+
+    import torch
+    shape = llama_like(1, 512, 4, 2, 128, 512)
+    B, L, nb = 1, 20, 512 * 4
+    _, _, toks, _, cache, ctx = _run(shape, B, L, 1, 1, "route_pinned")
+    hip = ctypes.CDLL("libamdhip64.so")
+    got = []
+    for i, flags in enumerate((0x0, 0x40000000, 0x80000000)):  # default, coherent, non-coherent
+        p = ctypes.c_void_p()
+        assert hip.hipHostMalloc(ctypes.byref(p), ctypes.c_size_t(3 * nb), ctypes.c_uint(flags)) == 0
+        ctypes.memset(p, 0, 3 * nb)
+        _step(ctx, 70 + i, toks[:, L], B, L, cache, p.value + nb)
+        ctx.vla_wait_boundary(70 + i, 60000)
+        whole = np.ctypeslib.as_array(ctypes.cast(p, ctypes.POINTER(ctypes.c_float)), (3 * 512,)).copy()
+        assert not whole[:512].any() and not whole[1024:].any()
+        got.append(whole[512:1024])
+        assert hip.hipHostFree(p) == 0
+    assert got[0].any() and all(np.array_equal(g, got[0]) for g in got)
+    ctx.vla_destroy()
