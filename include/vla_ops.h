@@ -58,6 +58,26 @@ vla_status vla_op_gemm_residual_bf16(const void *A, const void *Wp, float *H, co
 vla_status vla_op_gemm_bias_bf16(const void *A, const void *Wp, void *out, const float *bias, int M, int N, int K,
                                  int gelu, void *stream);
 
+/* How a product of the blocks runs, for tests and timings.  vla_op_gemm_route
+ * (host only, no GPU work): columns [0, *n1) in tiles of first[0] rows x
+ * first[1] columns by first[2] waves, the rest, if *n1 < N, in a second launch
+ * in tiles `second` (zeros if there is none); a_parts = 2 for a split operand.
+ * vla_op_gemm_tile_bf16 runs VLA_GEMM_RESIDUAL, _BIAS or _GELU (the
+ * arguments of the two entry points above) in the tile of these sizes
+ * whatever the choice; VLA_ERR_UNSUPPORTED if the product has no such tile,
+ * or only for whole multiples of its columns. */
+typedef enum {
+  VLA_GEMM_F32 = 0,      /* vla_op_gemm_bf16 */
+  VLA_GEMM_RESIDUAL = 1, /* output projection, down, fc2, patch embedding */
+  VLA_GEMM_BIAS = 2,     /* connector, second product */
+  VLA_GEMM_GELU = 3,     /* fc1; connector, first product */
+  VLA_GEMM_SWIGLU = 4,   /* gate/up (N = 2 d_ff, padded) */
+  VLA_GEMM_QKV = 5
+} vla_gemm_op;
+vla_status vla_op_gemm_route(int op, int M, int N, int K, int a_parts, int first[3], int *n1, int second[3]);
+vla_status vla_op_gemm_tile_bf16(int op, int rows, int cols, int waves, const void *A, const void *Wp, void *out,
+                                 const float *bias, int M, int N, int K, void *stream);
+
 /* y[M][d] (bf16) = RMSNorm(x[M][d] fp32; gain g[d] fp32, eps) -- or
  * LayerNorm with shift b[d] when b != NULL.  d % 4 == 0, d <= 8192. */
 vla_status vla_op_norm_bf16(const float *x, const float *g, const float *b, float eps, void *y, int M, int d,

@@ -25,6 +25,7 @@ STATUS = {0: "VLA_OK", -1: "VLA_ERR_INVALID_ARG", -2: "VLA_ERR_SHAPE", -3: "VLA_
 VLA_BF16, VLA_F32 = 0, 1
 VLA_STACK_LLM, VLA_STACK_ENC = 0, 1
 VLA_PREC_BF16, VLA_PREC_SPLIT = 0, 1
+VLA_GEMM_F32, VLA_GEMM_RESIDUAL, VLA_GEMM_BIAS, VLA_GEMM_GELU, VLA_GEMM_SWIGLU, VLA_GEMM_QKV = range(6)
 KERNEL_CLASSES = ["norm", "qkv", "attn", "oproj", "mlp_up", "mlp_down", "other", "stem", "connector"]
 
 
@@ -109,6 +110,9 @@ def lib():
             "vla_op_pack_weight_bf16": [c_void_p, c_void_p, c_int, c_int],
             "vla_op_gemm_residual_bf16": [c_void_p, c_void_p, c_void_p, c_void_p, c_int, c_int, c_int, c_void_p],
             "vla_op_gemm_bias_bf16": [c_void_p, c_void_p, c_void_p, c_void_p, c_int, c_int, c_int, c_int, c_void_p],
+            "vla_op_gemm_route": [c_int, c_int, c_int, c_int, c_int, P(c_int), P(c_int), P(c_int)],
+            "vla_op_gemm_tile_bf16": [c_int, c_int, c_int, c_int, c_void_p, c_void_p, c_void_p, c_void_p, c_int, c_int,
+                                      c_int, c_void_p],
             "vla_suffix_create": [P(vla_stack_cfg), c_int, c_int, c_int, P(c_void_p)],
             "vla_suffix_load_block_weights": [c_void_p, c_int, P(vla_block_weights)],
             "vla_suffix_run": [c_void_p, c_void_p, c_int, c_int, c_int, c_void_p],
@@ -379,6 +383,18 @@ def vla_op_gemm_residual_bf16(A, Wp, H, bias, M, N, K, stream=None):
 
 def vla_op_gemm_bias_bf16(A, Wp, out, bias, M, N, K, gelu, stream=None):
     _check(lib().vla_op_gemm_bias_bf16(_ptr(A), _ptr(Wp), _ptr(out), _ptr(bias), M, N, K, int(gelu), stream))
+
+
+def vla_op_gemm_route(op, M, N, K, a_parts=1):
+    """[(columns, (rows, cols, waves) of the tile)] of each launch."""
+    t = [(c_int * 3)(), (c_int * 3)()]
+    n1 = c_int()
+    _check(lib().vla_op_gemm_route(op, M, N, K, a_parts, t[0], ctypes.byref(n1), t[1]))
+    return [(n, tuple(x)) for n, x in ((n1.value, t[0]), (N - n1.value, t[1])) if n]
+
+
+def vla_op_gemm_tile_bf16(op, tile, A, Wp, out, bias, M, N, K, stream=None):
+    _check(lib().vla_op_gemm_tile_bf16(op, *tile, _ptr(A), _ptr(Wp), _ptr(out), _ptr(bias), M, N, K, stream))
 
 
 def vla_status_string(code: int) -> str:

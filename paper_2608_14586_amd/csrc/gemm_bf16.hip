@@ -725,30 +725,30 @@ enum TileId {
   T_64x64, T_64x128, T_128x128, T_128x128_PAIR, T_256x128, T_256x256, T_256x192, T_192x384, T_192x256, T_192x128, T_COUNT
 };
 struct TileCost {
-  int bm, bn, per_cu;
+  int bm, bn, waves, per_cu;
   bool whole_n;  // only for N a multiple of bn
   float t0, t1, t2, f;
   float step = 0.f;  // of t, as the first CU takes a second workgroup
 };
 constexpr TileCost kTiles[T_COUNT] = {
-    {64, 64, 2, false, 0.25f, 0.30f, 0.44f, 2.5f},     // 64 KB of LDS
-    {64, 128, 2, false, 0.38f, 0.46f, 0.82f, 3.5f},    // 72 KB
-    {128, 128, 1, false, 0.38f, 0.55f, 0.f, 5.f},      // 128 KB, 8 waves
+    {64, 64, 4, 2, false, 0.25f, 0.30f, 0.44f, 2.5f},     // 64 KB of LDS
+    {64, 128, 4, 2, false, 0.38f, 0.46f, 0.82f, 3.5f},    // 72 KB
+    {128, 128, 8, 1, false, 0.38f, 0.55f, 0.f, 5.f},      // 128 KB, 8 waves
     // 80 KB, 4 waves.  The step: the CUs with two set the time of a round that
     // gives the others one (gate/up of a 7B block over 203 tokens, 344 tiles,
     // 0.92 us a slab: 64.2 us, and 53.0 as 172 of 256x128; ViT fc2 at 6144
     // rows, 384 tiles, 0.91)
-    {128, 128, 2, false, 0.54f, 0.65f, 1.0f, 5.5f, 0.12f},
-    {256, 128, 1, false, 0.55f, 0.89f, 0.f, 7.f},      // 144 KB
-    {256, 256, 1, false, 1.07f, 1.31f, 0.f, 10.f},     // 160 KB
-    {256, 192, 1, true, 1.05f, 1.28f, 0.f, 10.f},      // 136 KB (QKV)
-    {192, 384, 1, true, 1.4f, 1.8f, 0.f, 20.f},        // 144 KB (QKV)
-    {192, 256, 1, true, 0.9f, 1.15f, 0.f, 11.f},       // 144 KB (GELU)
+    {128, 128, 4, 2, false, 0.54f, 0.65f, 1.0f, 5.5f, 0.12f},
+    {256, 128, 8, 1, false, 0.55f, 0.89f, 0.f, 7.f},      // 144 KB
+    {256, 256, 8, 1, false, 1.07f, 1.31f, 0.f, 10.f},     // 160 KB
+    {256, 192, 8, 1, true, 1.05f, 1.28f, 0.f, 10.f},      // 136 KB (QKV)
+    {192, 384, 8, 1, true, 1.4f, 1.8f, 0.f, 20.f},        // 144 KB (QKV)
+    {192, 256, 8, 1, true, 0.9f, 1.15f, 0.f, 11.f},       // 144 KB (GELU)
     // 120 KB.  One tile per CU where 128x128 gives half of the CUs two: 6144 x 1024, K = 4096 63.9 -> 54.3 us, 4300 x 1024
     // 55.2 -> 42.2, 1200 x 4096 49.6 -> 45.7, 1100 x 4096, K = 11008 118 -> 102;
     // QKV of a 7B block over 300 tokens and the connector over 1536 each about
     // 13 us less
-    {192, 128, 1, false, 0.32f, 0.71f, 0.f, 8.5f},
+    {192, 128, 8, 1, false, 0.32f, 0.71f, 0.f, 8.5f},
 };
 // Estimated us of an M x N product over nk slabs.
 inline float tile_us(const TileCost& c, int M, int N, int nk) {
@@ -781,71 +781,62 @@ hipError_t launch_tile(int id, const bf16_t* A, int lda, const WOperand& W, int 
   const TileCost& tc = kTiles[id];
   const int tiles_n = (n1 - n0 + tc.bn - 1) / tc.bn;
   const dim3 grid((unsigned)((long)((M + tc.bm - 1) / tc.bm) * tiles_n));
-  auto go = [&](auto kernel, int threads) {
-    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, A, lda, W, M, N, K, Kw, n0, tiles_n, e);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * tc.waves), 0, s, A, lda, W, M, N, K, Kw, n0, tiles_n, e);
   };
-#define VLA_TILE(id, nw, ...)                                                            \
-  case id:                                                                               \
-    if constexpr (tile_allowed<Epi>(id)) go(gemm_bf16_dma_kernel<__VA_ARGS__>, 64 * nw); \
+#define VLA_TILE(id, BM, BN, WM, WN, NW, ...)                                                                        \
+  case id:                                                                                                           \
+    static_assert(kTiles[id].bm == BM && kTiles[id].bn == BN && kTiles[id].waves == NW, "the table's tile");         \
+    if constexpr (tile_allowed<Epi>(id)) go(gemm_bf16_dma_kernel<BM, BN, WM, WN, NW, WT, Epi, __VA_ARGS__>); \
     break
   switch (id) {
-    VLA_TILE(T_64x64, 4, 64, 64, 32, 32, 4, WT, Epi, 4, 4);
-    VLA_TILE(T_64x128, 4, 64, 128, 32, 64, 4, WT, Epi, 3, 3);
-    VLA_TILE(T_128x128, 8, 128, 128, 32, 64, 8, WT, Epi, 4, 4);
-    VLA_TILE(T_128x128_PAIR, 4, 128, 128, 64, 64, 4, WT, Epi, 3);
-    VLA_TILE(T_256x128, 8, 256, 128, 64, 64, 8, WT, Epi, 3, 3);
-    VLA_TILE(T_256x256, 8, 256, 256, 128, 64, 8, WT, Epi, 3);
-    VLA_TILE(T_256x192, 8, 256, 192, 64, 96, 8, WT, Epi, 3);
-    VLA_TILE(T_192x384, 8, 192, 384, 96, 96, 8, WT, Epi);
-    VLA_TILE(T_192x256, 8, 192, 256, 96, 64, 8, WT, Epi, 3);
-    VLA_TILE(T_192x128, 8, 192, 128, 96, 32, 8, WT, Epi, 3, 3);
+    VLA_TILE(T_64x64, 64, 64, 32, 32, 4, 4, 4);
+    VLA_TILE(T_64x128, 64, 128, 32, 64, 4, 3, 3);
+    VLA_TILE(T_128x128, 128, 128, 32, 64, 8, 4, 4);
+    VLA_TILE(T_128x128_PAIR, 128, 128, 64, 64, 4, 3);
+    VLA_TILE(T_256x128, 256, 128, 64, 64, 8, 3, 3);
+    VLA_TILE(T_256x256, 256, 256, 128, 64, 8, 3);
+    VLA_TILE(T_256x192, 256, 192, 64, 96, 8, 3);
+    VLA_TILE(T_192x384, 192, 384, 96, 96, 8, 2);
+    VLA_TILE(T_192x256, 192, 256, 96, 64, 8, 3);
+    VLA_TILE(T_192x128, 192, 128, 96, 32, 8, 3, 3);
     default: return hipErrorInvalidValue;
   }
 #undef VLA_TILE
   return hipGetLastError();
 }
 
-// A [M][a_parts * K]: a_parts column blocks of K, each multiplied by the
-// same W [N][K] into one accumulator (2: a hi + lo operand pair).
-template <bool WT, class Epi>
-hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int K, const Epi& e, hipStream_t s,
-                  int a_parts = 1) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  if (K % BK != 0 || lda % 8 != 0 || a_parts < 1 || a_parts > 2 || lda < a_parts * K) return hipErrorInvalidValue;
-  if (WT) {
-    // every 256-column tile inside the packing, 32-bit byte offsets
-    if (W.nblk <= 0 || W.nblk % 2 || W.nblk * SLAB_N < N || (size_t)W.nblk * SLAB_N * K * 2 >= (1u << 31))
-      return hipErrorInvalidValue;
-  } else {
-    if (W.ld % 8 != 0 || W.ld < K || (size_t)256 * W.ld * 2 >= (1u << 31)) return hipErrorInvalidValue;
-  }
-  // byte offsets inside a tile's buffer resource are 32-bit
-  if ((size_t)256 * lda * 2 >= (1u << 31)) return hipErrorInvalidValue;
-  // the cheapest tile of the epilogue's set
-  const int nk = a_parts * K / BK;
-  int best = -1;
+// How a product runs: columns [0, n1) in tile `first`, the rest in tile
+// `second` (n1 = N: one launch).
+struct Route {
+  int first, n1, second;
+};
+// The cheapest tile of the epilogue's set, or two launches.
+//
+// Two launches: the columns that fill whole rounds of a large tile, and the
+// rest in the tile that suits them, where the whole in one tile would end
+// in a round of few workgroups.  Gate/up of a 7B block (22016 columns) over
+// 1001 tokens is 344 tiles of 256x256, 256 in the first round and 88 in the
+// second.  The estimate must gain 10 us, what the second launch's drain and
+// ramp cost (fc1 at 5120 rows, estimated 8 us less, measured 4 us more), and
+// 3%.  us less a 7B block: 700 tokens 24, 1024 17, 1350 43; with split
+// operands 700 tokens 53, 1001 35, 1400 86; four 0.5B blocks of 1900 tokens
+// 39, of 3400 53.  Not where the best tile runs two a CU and only a few are
+// left for its last round: those start as their CUs come free, and the
+// estimate has them too dear (0.5B over 1700 tokens, 40 of 512 left: 520 us
+// in one launch, 528 in two).  Residual products keep to one launch.
+template <class Epi>
+Route choose(int M, int N, int nk) {
+  Route r{-1, N, -1};
   float best_us = 0.f;
   for (int i = 0; i < T_COUNT; ++i) {
     if (!tile_allowed<Epi>(i) || (kTiles[i].whole_n && N % kTiles[i].bn)) continue;
     const float us = tile_us(kTiles[i], M, N, nk);
-    if (best < 0 || us < best_us) best = i, best_us = us;
+    if (r.first < 0 || us < best_us) r.first = i, best_us = us;
   }
-  // Two launches: the columns that fill whole rounds of a large tile, and the
-  // rest in the tile that suits them, where the whole in one tile would end
-  // in a round of few workgroups.  Gate/up of a 7B block (22016 columns) over
-  // 1001 tokens is 344 tiles of 256x256, 256 in the first round and 88 in the
-  // second.  The estimate must gain 10 us, what the second launch's drain and
-  // ramp cost (fc1 at 5120 rows, estimated 8 us less, measured 4 us more), and
-  // 3%.  us less a 7B block: 700 tokens 24, 1024 17, 1350 43; with split
-  // operands 700 tokens 53, 1001 35, 1400 86; four 0.5B blocks of 1900 tokens
-  // 39, of 3400 53.  Not where the best tile runs two a CU and only a few are
-  // left for its last round: those start as their CUs come free, and the
-  // estimate has them too dear (0.5B over 1700 tokens, 40 of 512 left: 520 us
-  // in one launch, 528 in two).  Residual products keep to one launch.
-  int big = -1, n1 = 0, rest = -1;
   if constexpr (!Epi::kDirect) {
     float two_us = 0.97f * best_us - 10.f;
-    const TileCost& bc = kTiles[best];
+    const TileCost& bc = kTiles[r.first];
     if (bc.per_cu == 2 && (long)((M + bc.bm - 1) / bc.bm) * ((N + bc.bn - 1) / bc.bn) % 512 < 64) two_us = 0.f;
     for (int i = T_256x256; i <= T_192x256; ++i) {
       const TileCost& c = kTiles[i];
@@ -857,15 +848,49 @@ hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int
       for (int j = 0; j < T_COUNT; ++j) {
         if (!tile_allowed<Epi>(j) || (kTiles[j].whole_n && (N - cols) % kTiles[j].bn)) continue;
         const float us = first + tile_us(kTiles[j], M, N - (int)cols, nk);
-        if (us < two_us) two_us = us, big = i, n1 = (int)cols, rest = j;
+        if (us < two_us) two_us = us, r = Route{i, (int)cols, j};
       }
     }
   }
-  if (big >= 0) {
-    const hipError_t err = launch_tile<WT>(big, A, lda, W, M, N, a_parts * K, K, 0, n1, e, s);
-    return err != hipSuccess ? err : launch_tile<WT>(rest, A, lda, W, M, N, a_parts * K, K, n1, N, e, s);
+  return r;
+}
+
+// A [M][a_parts * K]: a_parts column blocks of K, each multiplied by the
+// same W [N][K] into one accumulator (2: a hi + lo operand pair).  tile >= 0:
+// in that tile whatever the estimate.
+template <bool WT, class Epi>
+hipError_t launch(const bf16_t* A, int lda, const WOperand& W, int M, int N, int K, const Epi& e, hipStream_t s,
+                  int a_parts = 1, int tile = -1) {
+  if (M <= 0 || N <= 0) return hipSuccess;
+  if (K % BK != 0 || lda % 8 != 0 || a_parts < 1 || a_parts > 2 || lda < a_parts * K) return hipErrorInvalidValue;
+  if (WT) {
+    // every column inside the packing, 32-bit byte offsets.  A tile's columns
+    // past the packing (a second launch starts at any multiple of 64) read
+    // the next slab, or zeros past the last one, and are not stored.
+    if (W.nblk <= 0 || W.nblk % 2 || W.nblk * SLAB_N < N || (size_t)W.nblk * SLAB_N * K * 2 >= (1u << 31))
+      return hipErrorInvalidValue;
+  } else {
+    if (W.ld % 8 != 0 || W.ld < K || (size_t)256 * W.ld * 2 >= (1u << 31)) return hipErrorInvalidValue;
   }
-  return launch_tile<WT>(best, A, lda, W, M, N, a_parts * K, K, 0, N, e, s);
+  // byte offsets inside a tile's buffer resource are 32-bit
+  if ((size_t)256 * lda * 2 >= (1u << 31)) return hipErrorInvalidValue;
+  Route r{tile, N, -1};
+  if (tile < 0)
+    r = choose<Epi>(M, N, a_parts * K / BK);
+  else if (tile >= T_COUNT || !tile_allowed<Epi>(tile) || (kTiles[tile].whole_n && N % kTiles[tile].bn))
+    return hipErrorInvalidValue;
+  hipError_t err = launch_tile<WT>(r.first, A, lda, W, M, N, a_parts * K, K, 0, r.n1, e, s);
+  if (err == hipSuccess && r.n1 < N) err = launch_tile<WT>(r.second, A, lda, W, M, N, a_parts * K, K, r.n1, N, e, s);
+  return err;
+}
+
+// launch()'s tile argument: -1 by the estimate, T_COUNT (refused) for a tile
+// that is not in the table
+int forced(const GemmTile* t) {
+  if (!t) return -1;
+  int i = 0;
+  while (i < T_COUNT && (kTiles[i].bm != t->rows || kTiles[i].bn != t->cols || kTiles[i].waves != t->waves)) ++i;
+  return i;
 }
 
 }  // namespace
@@ -876,10 +901,10 @@ hipError_t gemm_bf16_store_f32(const bf16_t* A, int lda, const bf16_t* W, int ld
 }
 
 hipError_t gemm_bf16_residual(const bf16_t* A, int lda, const WOperand& W, float* H, int ldh, const float* bias, int M,
-                              int N, int K, hipStream_t s, int a_parts) {
+                              int N, int K, hipStream_t s, int a_parts, const GemmTile* t) {
   // the residual epilogue addresses a wave's rows with 32-bit byte offsets
   if (N % 4 || ldh % 4 || (size_t)256 * ldh * 4 >= (1u << 31)) return hipErrorInvalidValue;
-  return launch<true>(A, lda, W, M, N, K, EpiResidual{H, bias, ldh, M, N}, s, a_parts);
+  return launch<true>(A, lda, W, M, N, K, EpiResidual{H, bias, ldh, M, N}, s, a_parts, forced(t));
 }
 
 hipError_t gemm_bf16_swiglu(const bf16_t* A, int lda, const WOperand& W, bf16_t* out, int ldo, int M, int N, int K,
@@ -891,21 +916,41 @@ hipError_t gemm_bf16_swiglu(const bf16_t* A, int lda, const WOperand& W, bf16_t*
 }
 
 hipError_t gemm_bf16_gelu(const bf16_t* A, int lda, const WOperand& W, bf16_t* out, int ldo, const float* bias, int M,
-                          int N, int K, hipStream_t s) {
+                          int N, int K, hipStream_t s, const GemmTile* t) {
   if (N % 8 || ldo % 8) return hipErrorInvalidValue;
-  return launch<true>(A, lda, W, M, N, K, EpiGelu{out, bias, ldo, M, N}, s);
+  return launch<true>(A, lda, W, M, N, K, EpiGelu{out, bias, ldo, M, N}, s, 1, forced(t));
 }
 
 hipError_t gemm_bf16_bias(const bf16_t* A, int lda, const WOperand& W, bf16_t* out, int ldo, const float* bias, int M,
-                          int N, int K, hipStream_t s) {
+                          int N, int K, hipStream_t s, const GemmTile* t) {
   if (N % 8 || ldo % 8) return hipErrorInvalidValue;
-  return launch<true>(A, lda, W, M, N, K, EpiStoreBF16{out, bias, ldo, M, N}, s);
+  return launch<true>(A, lda, W, M, N, K, EpiStoreBF16{out, bias, ldo, M, N}, s, 1, forced(t));
 }
 
 hipError_t gemm_bf16_qkv(const bf16_t* A, int lda, const WOperand& W, const QkvArgs& qa, int M, int N, int K,
                          hipStream_t s, int a_parts) {
   if (qa.dh % 64 != 0 || N % 64 != 0) return hipErrorInvalidValue;
   return launch<true>(A, lda, W, M, N, K, EpiQKV{qa, M}, s, a_parts);
+}
+
+hipError_t gemm_bf16_route(GemmOp op, int M, int N, int K, int a_parts, GemmTile* first, int* n1, GemmTile* second) {
+  if (M <= 0 || N <= 0 || K <= 0 || K % BK || a_parts < 1 || a_parts > 2) return hipErrorInvalidValue;
+  const int nk = a_parts * K / BK;
+  Route r;
+  switch (op) {
+    case GemmOp::F32: r = choose<EpiStoreF32>(M, N, nk); break;
+    case GemmOp::RESIDUAL: r = choose<EpiResidual>(M, N, nk); break;
+    case GemmOp::BIAS: r = choose<EpiStoreBF16>(M, N, nk); break;
+    case GemmOp::GELU: r = choose<EpiGelu>(M, N, nk); break;
+    case GemmOp::SWIGLU: r = choose<EpiSwiGLU>(M, N, nk); break;
+    case GemmOp::QKV: r = choose<EpiQKV>(M, N, nk); break;
+    default: return hipErrorInvalidValue;
+  }
+  auto tile = [](int i) { return i < 0 ? GemmTile{} : GemmTile{kTiles[i].bm, kTiles[i].bn, kTiles[i].waves}; };
+  *first = tile(r.first);
+  *n1 = r.n1;
+  *second = tile(r.second);
+  return hipSuccess;
 }
 
 }  // namespace vla

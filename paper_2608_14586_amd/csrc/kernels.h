@@ -40,6 +40,17 @@ struct WOperand {
   int nblk;
 };
 
+// A tile of the products below, by its sizes; the products take the one their
+// estimate chooses, or *t where a test or a timing names one (refused if the
+// product has no such tile).
+struct GemmTile {
+  int rows = 0, cols = 0, waves = 0;
+};
+enum class GemmOp { F32, RESIDUAL, BIAS, GELU, SWIGLU, QKV };
+// How op runs over M rows, N columns and a_parts column blocks of K: columns
+// [0, *n1) in tile *first, the rest (none: *n1 = N) in *second.  Host only.
+hipError_t gemm_bf16_route(GemmOp op, int M, int N, int K, int a_parts, GemmTile* first, int* n1, GemmTile* second);
+
 // C (fp32) = acc, W row-major [N][ldw] (ldw % 8 == 0)
 hipError_t gemm_bf16_store_f32(const bf16_t* A, int lda, const bf16_t* W, int ldw, float* C, int ldc, int M,
                                int N, int K, hipStream_t s);
@@ -49,7 +60,7 @@ hipError_t gemm_bf16_store_f32(const bf16_t* A, int lda, const bf16_t* W, int ld
 // MFMA work of a plain bf16 operand and a 16-bit significand in its place.
 // H (fp32 residual) += acc + bias (bias may be NULL)
 hipError_t gemm_bf16_residual(const bf16_t* A, int lda, const WOperand& W, float* H, int ldh, const float* bias,
-                              int M, int N, int K, hipStream_t s, int a_parts = 1);
+                              int M, int N, int K, hipStream_t s, int a_parts = 1, const GemmTile* t = nullptr);
 // out (bf16) [M][N/2] = silu(gate) * up, W rows interleaved in groups of 32
 // (32 gate rows, then the 32 up rows of the same features); N % 64 == 0.
 // lo_col > 0: the remainder bf16(y - bf16(y)) of each output also goes to
@@ -58,7 +69,7 @@ hipError_t gemm_bf16_swiglu(const bf16_t* A, int lda, const WOperand& W, bf16_t*
                             hipStream_t s, int a_parts = 1, int lo_col = 0);
 // out (bf16) = gelu_erf(acc + bias)
 hipError_t gemm_bf16_gelu(const bf16_t* A, int lda, const WOperand& W, bf16_t* out, int ldo, const float* bias,
-                          int M, int N, int K, hipStream_t s);
+                          int M, int N, int K, hipStream_t s, const GemmTile* t = nullptr);
 
 // Fused QKV projection epilogue.  Packed weight rows: [q heads | k heads |
 // v heads], each head's head_dim rows in 64-row groups that hold 32 rows of
@@ -81,7 +92,7 @@ hipError_t gemm_bf16_qkv(const bf16_t* A, int lda, const WOperand& W, const QkvA
 
 // out (bf16) = acc + bias (bias may be NULL); N % 8 == 0, ldo % 8 == 0
 hipError_t gemm_bf16_bias(const bf16_t* A, int lda, const WOperand& W, bf16_t* out, int ldo, const float* bias,
-                          int M, int N, int K, hipStream_t s);
+                          int M, int N, int K, hipStream_t s, const GemmTile* t = nullptr);
 
 // ---------------------------------------------------------- vision stem
 // Patch rows of n_img images [C][H][W] cut into p x p patches (row-major

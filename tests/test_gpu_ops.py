@@ -37,8 +37,9 @@ def _packed(W, N, K):
     return _dev_bf16(vb.vla_op_pack_weight_bf16(W, N, K))
 
 
-# ViT proj / fc2 (also over ragged rows), decoder O-projection / down at
-# L=2048 and L=1024, ragged rows and columns, single rows.
+# The rows and columns of ViT proj / fc2 (also over ragged rows) and of the
+# decoder O-projection / down at L=2048 (128x128 tiles at this short K) and
+# L=1024 (64x128), ragged rows and columns, single rows.
 @pytest.mark.parametrize("M,N,K,bias", [(6144, 1024, 128, True), (6100, 1024, 64, True), (2048, 4096, 192, False),
                                         (1024, 4096, 128, False), (6104, 1000, 192, True), (77, 96, 64, True),
                                         (1, 4, 64, True), (130, 8, 128, False)])
@@ -70,8 +71,10 @@ def test_gemm_residual_bf16(M, N, K, bias):
     assert (err <= bound).all(), (worst, err[worst], bound[worst])
 
 
-# 192x256 tiles with 8 waves in whole rounds (ViT fc1), the same over ragged
-# rows, 256x256 tiles (two rounds and more), 64x128 tiles, single rows.
+# ViT fc1's rows and columns, the same over ragged rows (at this short K both
+# take 128x128 tiles), 256x256 tiles over two rounds, 64x64 tiles, single rows.
+# (Every tile of every epilogue, 192x256 over ragged rows among them:
+# test_gpu_tiles.py; which shape takes which: test_gemm_routes.py.)
 @pytest.mark.parametrize("M,N,K,bias,gelu", [(6144, 4096, 128, True, True), (6000, 4096, 64, True, True),
                                              (2048, 16384, 64, True, False), (300, 1000, 128, True, True),
                                              (77, 96, 64, False, False), (1, 8, 64, False, True)])
@@ -111,8 +114,9 @@ def _sample_rows(M, tag, n=24):
 
 
 # The products at their full K, in the launch configuration of the bench
-# frame: decoder down (K = 11008, 172 k-slabs) and O-projection (K = 4096),
-# ViT fc2 (K = 4096) with its bias; sampled rows against float64.
+# frame: decoder down (K = 11008, 172 k-slabs) and O-projection (K = 4096) on
+# 256x128 tiles, ViT fc2 (K = 4096) with its bias on 192x128; sampled rows
+# against float64.
 @pytest.mark.parametrize("M,N,K,bias", [(2048, 4096, 11008, False), (2048, 4096, 4096, False),
                                         (6144, 1024, 4096, True)])
 def test_gemm_residual_bf16_full_k(M, N, K, bias):
@@ -146,8 +150,8 @@ def test_gemm_residual_bf16_full_k(M, N, K, bias):
     assert e < 1e-5, e
 
 
-# ViT fc1 + GELU at its full K and the plain bias product over a two-round
-# 256x256 grid; sampled rows.
+# ViT fc1 + GELU at its full K (192x256 tiles, two whole rounds) and the plain
+# bias product over a two-round 256x256 grid; sampled rows.
 @pytest.mark.parametrize("M,N,K,gelu", [(6144, 4096, 1024, True), (2048, 16384, 4096, False)])
 def test_gemm_bias_gelu_bf16_full_k(M, N, K, gelu):
     import torch

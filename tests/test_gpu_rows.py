@@ -27,8 +27,11 @@ def _prefix(ctx, s, dt, tok, k, frame):
     return bnd.hidden.numpy().copy(), _bits(bnd.kv)
 
 
-# long K with few rows and with many: 7B down (K = 11008), 0.5B down (K = 4864)
-@pytest.mark.parametrize("name,L,B,longer", [("llm7b", 16, 3, 203), ("llm7b", 203, 2, 1000), ("small_llm", 65, 4, 700),
+# long K with few rows and with many: 7B down (K = 11008), 0.5B down (K =
+# 4864); gate/up in two launches at 1000 rows, QKV (rotary embedding, K, V and
+# V^T behind columns that another launch wrote) at 1601 split and at 2113
+@pytest.mark.parametrize("name,L,B,longer", [("llm7b", 16, 3, 203), ("llm7b", 203, 2, 1000), ("llm7b", 512, 1, 1601),
+                                             ("llm7b", 1000, 1, 2113), ("small_llm", 65, 4, 700),
                                              ("small_llm", 333, 2, 2000)])
 @pytest.mark.parametrize("split", [False, True])
 def test_prefix_rows_alone_and_together(name, L, B, longer, split):

@@ -5,7 +5,9 @@ import pytest
 
 import oracle
 import synth
+from paper_2608_14586_amd import binding as vb
 from prefix_cases import EncCase, LlmCase, rel_l2, to_f32
+from test_gemm_routes import T192x256, TILES
 
 pytestmark = pytest.mark.gpu
 
@@ -15,15 +17,14 @@ def _dev(a):
     return torch.from_numpy(np.ascontiguousarray(a).view(np.int16) if a.dtype == np.uint16 else a.copy()).cuda()
 
 
-# K from one slab to past every ring's depth; rows and columns on and off the
-# tile edges of 64, 128 and 256; grids of a few workgroups, about one per CU,
-# about two, and several rounds
+# the tiles the estimate takes at short K (64x64, 64x128 and 128x128, 256x256
+# for the two widest GELU grids): rows and columns on and off the tile edges,
+# grids of a few workgroups, about one per CU, about two, and several rounds
 @pytest.mark.parametrize("M,N,K", [(1, 96, 64), (19, 4096, 128), (64, 896, 192), (65, 1152, 256), (130, 4096, 320),
                                    (203, 1000, 384), (257, 3072, 448), (513, 4096, 512), (1001, 4096, 192),
                                    (1154, 1024, 1024), (1300, 9728, 128), (2050, 4096, 256)])
 def test_products_over_tiles(M, N, K):
     import torch
-    from paper_2608_14586_amd import binding as vb
     A = synth.normal_bf16(synth.seed_of("tileA", M, N, K), (M, K))
     W = synth.normal_bf16(synth.seed_of("tileW", M, N, K), (N, K))
     b = synth.normal_f32(synth.seed_of("tileb", M, N, K), (N,))
@@ -46,6 +47,57 @@ def test_products_over_tiles(M, N, K):
     err = np.abs(synth.as_f32(out.cpu().numpy().view(np.uint16)) - ref)
     bound = 2.0 ** -8 * np.abs(ref) + 1.2 * acc + 2e-7 * np.abs(z)
     assert (err <= bound).all(), np.unravel_index(np.argmax(err - bound), err.shape)
+
+
+# Every tile of every epilogue, whatever the estimate takes it for: one row, one
+# off and two past a tile's edge in rows, columns cut inside the tile (whole
+# tiles where it is only for those), K of one slab to one past the deepest ring
+# (four slabs).  Element by element; nothing beside the output is written.
+@pytest.mark.parametrize("op,tile", [(op, t) for op in (vb.VLA_GEMM_RESIDUAL, vb.VLA_GEMM_BIAS, vb.VLA_GEMM_GELU)
+                                     for t in TILES[op]])
+def test_each_tile(op, tile):
+    import torch
+    bm, bn, _ = tile
+    whole = tile == T192x256
+    tag = ("each", op) + tile
+    Ns = [2 * bn] if whole else [8, bn - 8, bn + 8, 2 * bn]
+    A = synth.normal_bf16(synth.seed_of("A", *tag), (2 * bm + 2, 320))
+    W = synth.normal_bf16(synth.seed_of("W", *tag), (2 * bn, 320), std=0.3)
+    b = synth.normal_f32(synth.seed_of("b", *tag), (2 * bn,))
+    H0 = synth.normal_f32(synth.seed_of("H", *tag), (2 * bm + 2, 2 * bn))
+    a64, w64 = synth.as_f32(A).astype(np.float64), synth.as_f32(W).astype(np.float64)
+    for i, (M, K) in enumerate([(1, 128), (bm - 1, 320), (bm, 64), (bm + 1, 192), (2 * bm + 2, 256)]):
+        N = Ns[i % len(Ns)]
+        dA = _dev(np.ascontiguousarray(A[:M, :K]))
+        dW = _dev(vb.vla_op_pack_weight_bf16(np.ascontiguousarray(W[:N, :K]), N, K))
+        bias = _dev(b[:N]) if i % 2 == 0 else None
+        z = a64[:M, :K] @ w64[:N, :K].T + (b[:N] if i % 2 == 0 else 0.0)
+        mag = np.abs(a64[:M, :K]) @ np.abs(w64[:N, :K]).T
+        if op == vb.VLA_GEMM_RESIDUAL:
+            out = torch.full((M * N + 4096,), 7.0, device="cuda")
+            out[:M * N] = _dev(H0[:M, :N]).reshape(-1)
+            guard, ref = 7.0, H0[:M, :N] + z
+        else:
+            out = torch.full((M * N + 4096,), 7.0, dtype=torch.bfloat16, device="cuda")
+            guard, ref = 7.0, oracle.gelu_erf(z) if op == vb.VLA_GEMM_GELU else z
+        vb.vla_op_gemm_tile_bf16(op, tile, dA, dW, out, bias, M, N, K)
+        torch.cuda.synchronize()
+        got = out.float().cpu().numpy()
+        assert (got[M * N:] == guard).all(), (M, N, K)
+        err = np.abs(got[:M * N].reshape(M, N) - ref)
+        # fp32 accumulation (K / 16 <= 20 roundings of the running sum, 2^-24
+        # each, with a factor 4) and the sums after it; for bf16 outputs one
+        # rounding (2^-9, with a factor 2) behind GELU's slope (<= 1.13) and
+        # the erfc approximation (1.5e-7 on Phi)
+        acc = 80 * 2.0 ** -24 * mag + 2.0 ** -22 * (np.abs(z) + np.abs(ref))
+        bound = acc if op == vb.VLA_GEMM_RESIDUAL else 2.0 ** -8 * np.abs(ref) + 1.2 * acc + 2e-7 * np.abs(z)
+        worst = np.unravel_index(np.argmax(err - bound), err.shape)
+        assert (err <= bound).all(), ((M, N, K), worst, err[worst], bound[worst])
+    # a tile that is not this product's, or not for these columns, is refused
+    for t in [(256, 192, 8), (128, 64, 4)] + ([tile] if whole else []):
+        with pytest.raises(vb.VlaError) as e:
+            vb.vla_op_gemm_tile_bf16(op, t, dA, dW, out, bias, M, 24, K)
+        assert e.value.name == "VLA_ERR_UNSUPPORTED"
 
 
 @pytest.mark.parametrize("name,L,B", [("small_llm", 1, 1), ("small_llm", 19, 1), ("small_llm", 65, 2),
@@ -87,7 +139,6 @@ def test_encoder_blocks_of_few_rows(n_img, L):
                                               (100, 4, 2, 6, 77, 1, 1), (256, 4, 4, 64, 688, 130, 1),
                                               (132, 2, 1, 66, 31, 16, 3), (512, 8, 2, 64, 8200, 200, 1)])
 def test_fp32_path_odd_shapes(d, H, Hkv, dh, F, L, B):
-    from paper_2608_14586_amd import binding as vb
     s = synth.configs.llama_like(2, d, H, Hkv, dh, F)
     wl = synth.Workload("tile_f32_%d_%d" % (d, F), "f32", s, None, batch=B, seq=L)
     W = [synth.llm_block_weights(wl, l, perturbed=True) for l in range(2)]
@@ -115,7 +166,6 @@ def test_fp32_path_odd_shapes(d, H, Hkv, dh, F, L, B):
                                  (130, 4), (333, 2)])
 def test_sequences_side_by_side(L, B):
     import torch
-    from paper_2608_14586_amd import binding as vb
     s = synth.configs.llama_like(2, 256, 4, 2, 64, 384)
     wl = synth.Workload("tile_seqs", "bf16", s, None, batch=B, seq=L)
     ctx = vb.Context(llm=vb.stack_cfg(s, "bf16", max_tokens=L, max_batch=B))
@@ -143,7 +193,6 @@ def test_sequences_side_by_side(L, B):
 @pytest.mark.parametrize("M,N,K", [(1345, 4000, 4096), (1153, 4096, 4096), (4801, 1024, 4096)])
 def test_residual_192_row_tiles(M, N, K):
     import torch
-    from paper_2608_14586_amd import binding as vb
     A = synth.normal_bf16(synth.seed_of("t192A", M, N, K), (M, K))
     W = synth.normal_bf16(synth.seed_of("t192W", M, N, K), (N, K))
     H0 = synth.normal_f32(synth.seed_of("t192H", M, N, K), (M, N))
@@ -166,7 +215,6 @@ def test_residual_192_row_tiles(M, N, K):
 @pytest.mark.parametrize("M,N,K,cut", [(1001, 22016, 4096, 4096), (700, 22016, 4096, 8192), (4206, 4096, 1024, 512)])
 def test_products_in_two_launches(M, N, K, cut):
     import torch
-    from paper_2608_14586_amd import binding as vb
     A = synth.normal_bf16(synth.seed_of("twoA", M, N, K), (M, K))
     W = synth.normal_bf16(synth.seed_of("twoW", M, N, K), (N, K))
     b = synth.normal_f32(synth.seed_of("twob", M, N, K), (N,))
