@@ -217,31 +217,6 @@ struct EpiSwiGLU {
   int ldo, M, N, lo;
   template <int TM, int TN>
   __device__ void operator()(const Acc<TM, TN>&, int, int, int) const {}  // LDS path only
-  template <int R, int NC>
-  __device__ void drain(const float* T, int m0, int n0, int tid) const {
-    // R rows x NC/16 chunks of 8 output features (4 chunks per 64-column group)
-    constexpr int CH = NC / 16;
-    static_assert((R * CH) % 256 == 0, "tile must split evenly over the workgroup");
-#pragma unroll
-    for (int j = 0; j < R * CH / 256; ++j) {
-      const int f = tid + 256 * j, row = f / CH, c = f % CH;
-      const int gsel = c >> 2, w = (c & 3) * 8;  // 64-column group, offset inside its 32
-      const int gr = m0 + row;
-      if (gr >= M || n0 + gsel * 64 >= N) continue;
-      const float* tr = T + row * NC + gsel * 64 + w;
-      f32x4 g0 = ld4(tr), g1 = ld4(tr + 4), u0 = ld4(tr + 32), u1 = ld4(tr + 36);
-      f32x4 y0, y1;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        y0[e] = silu(g0[e]) * u0[e];
-        y1[e] = silu(g1[e]) * u1[e];
-      }
-      bf16_t* dst = out + (size_t)gr * ldo + (n0 >> 1) + gsel * 32 + w;
-      const u32x4 hi = pack8(y0, y1);
-      *(u32x4*)dst = hi;
-      if (lo) *(u32x4*)(dst + lo) = pack8(y0 - unpack_lo4(hi, 0), y1 - unpack_lo4(hi, 2));
-    }
-  }
   // Y: R x NC fp32 activations (row stride NC) of the tile at (m0, feature
   // n0 / 2); 256 threads, chunks of 8 features.
   template <int R, int NC>
