@@ -147,7 +147,8 @@ vla_status vla_load_block_weights(vla_ctx *ctx, vla_stack which, int block, cons
  * on this context starts only after this run's output is written (so out_dev
  * may be its tokens), and this run writes out_dev only after the latest
  * earlier prefix has read its input (so one buffer may carry every frame).
- * Other readers of out_dev order themselves after the encoder stream. */
+ * Other readers of out_dev order themselves after the encoder stream.  As in
+ * vla_run_prefix, an image's result does not depend on the others. */
 vla_status vla_run_encoder(vla_ctx *ctx, uint64_t frame_id, const void *patches, int n_img, int L_img,
                            void *out_dev);
 
@@ -219,7 +220,9 @@ vla_status vla_run_vision(vla_ctx *ctx, uint64_t frame_id, const void *images, i
  * blocks are copied to `out` on the copy stream, each layer's KV as soon as
  * that layer has written it.  k = 0 hands back the input (Eq. (5) with no
  * blocks).  Enqueued; returns after launch.  Equivalent to
- * vla_run_blocks(ctx, frame_id, tokens, <stack dtype>, B, L, 0, k, out). */
+ * vla_run_blocks(ctx, frame_id, tokens, <stack dtype>, B, L, 0, k, out).
+ * A sequence's boundary and KV do not depend on the others of its call, to
+ * the last bit: the sums of a row run in one order whatever B is. */
 vla_status vla_run_prefix(vla_ctx *ctx, uint64_t frame_id, const void *tokens, int B, int L, int k,
                           vla_boundary *out);
 

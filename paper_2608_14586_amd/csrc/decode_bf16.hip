@@ -30,17 +30,19 @@
 //    residual add.
 //  * gemv_chunk_kernel: the same product staging the input chunk by chunk
 //    (2048 k at a time, a barrier around each), for inputs too wide for the
-//    streaming kernel's LDS (four rows of a d_ff-wide input) or shorter than
-//    half a chunk.  (d=896 products on the streaming kernel: QKV 5.6 -> 5.1
-//    us, and the gate/up product there needs no SwiGLU launch of its own.)
+//    streaming kernel's 96 KB of LDS (eight staged rows, four sequences with
+//    split operands, of a d_ff-wide input; four rows of 11008 just fit) or
+//    shorter than half a chunk.  (d=896 products on the streaming kernel: QKV
+//    5.6 -> 5.1 us, and the gate/up product there needs no SwiGLU launch of
+//    its own.)
 //  * attn_decode_kernel: one workgroup per (sequence, head, 128-key split);
 //    applies RoPE to q and to the new key at the token's position, appends the
 //    new key and value to the cache, and writes (max, sum, unnormalised
 //    output) partials that a small kernel combines into the bf16 attention
 //    output -- or, for few heads and splits, the O-projection while it stages
-//    its input (d=896 at position 700: 3.7 + 3.0 us and a launch's gap -> 4.8).
-//     (Combining in the last workgroup of each head, found with a
-//    device-scope counter, needs an L2 write-back per workgroup on this
+//    its input (d=896 at position 700: 3.7 + 3.0 us and a launch's gap -> 5.5;
+//    4.8 in an order of sums of its own).  (Combining in the last workgroup of
+//    each head, found with a device-scope counter, needs an L2 write-back per workgroup on this
 //    multi-XCD part and measured 3x slower than the extra launch.)
 // Rounding points follow the prefill: normed activations, q and K/V after
 // RoPE, the attention output and the gated activation are bf16.  With split

@@ -19,9 +19,9 @@ namespace {
 // its chain of loads is a quarter as long; otherwise they take the four
 // quadrants of a 64x64 tile.  Both sum the quarters on their own and add them
 // in the same order, so that a row's bits do not depend on how many rows share
-// the call.  A 128-row product of the d=256 stack (K = 256
-// and 688) took 57 us with 64x64 VALU tiles in 16-deep LDS slabs (8 to 24
-// workgroups, two barriers a slab) and takes 8.
+// the call.  A 128-row product of the d=256 stack (K = 256 and 688) took 57 us
+// with 64x64 VALU tiles in 16-deep LDS slabs (8 to 24 workgroups, two barriers
+// a slab) and takes 6 to 9 under the tracer.
 // VEC: rows are 16-byte aligned; otherwise elements load one by one.
 template <bool SPLIT, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda,
@@ -147,7 +147,7 @@ __global__ void qkv_split_f32_kernel(const float* __restrict__ qkv, const float*
 // query's output dims.  dh <= DH, the dims past it are zeros.  (One thread
 // per query, its q and output rows in registers over all keys, took 844 us at
 // L = 128, 4 heads of 64: eight waves in all, each a serial chain over the
-// keys; this takes 17.)
+// keys; this takes 17 to 18.)
 constexpr int AF_Q = 16, AF_K = 64;
 template <int DH>
 __global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,

@@ -680,8 +680,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
 // split over workgroups: every row's sums run over K in one order in every
 // tile, so a row's bits do not depend on how many rows share the call.  (With
 // K split by the row count a 7B block over 203 tokens took 190 us instead of
-// 200, over 1001 with split operands 750 instead of 783, and a sequence had
-// other bits in a batch than alone.)
+// 200, over 16 125 instead of 152, over 1001 with split operands 750 instead
+// of 783, and a sequence had other bits in a batch than alone.)
 // The estimate: a workgroup spends t us on each of its 64-k slabs and f us on
 // its prologue and epilogue; workgroups run in rounds of 256 (one per CU) or
 // 512 (two per CU), and t grows with the number that run together, since they
@@ -690,9 +690,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_dma_kernel(const bf16_t* __
 // 0.5B and ViT-L products with their weights read from HBM (mean error
 // 6-11%).  What the choice gives against one
 // rule on the tile count (64x128 two-slot tiles up to half a round of
-// 128x128, those up to 512 tiles of 256x256), us:
-//   O-projection M=2048 71.7 -> 67; down M=2048 185 -> 161
-//   7B QKV       M=203 57   -> 38, gate/up M=512 131 -> 90, M=1024 203 -> 171
+// 128x128, those up to 512 tiles of 256x256), us with the weights from HBM,
+// the first two rows trains of one product over several copies of its
+// weights, the others by event pairs inside a 7B block:
+//   O-projection M=203 51 -> 20, M=1001 57 -> 40, M=2048 73 -> 68
+//   down         M=203 130 -> 45, M=1001 141 -> 99, M=2048 180 -> 165
+//   QKV          M=203 61 -> 42, M=512 76 -> 61
+//   gate/up      M=203 71 -> 57, M=512 130 -> 89, M=1024 200 -> 161
 // Few workgroups leave each CU waiting on the latency of its own slab loads,
 // so the small tiles keep a ring of 3-4 slabs of both operands; large grids
 // are bound by L2 -> LDS traffic and want the large tiles.
@@ -710,19 +714,21 @@ constexpr TileCost kTiles[T_COUNT] = {
     {64, 128, 4, 2, false, 0.38f, 0.46f, 0.82f, 3.5f},    // 72 KB
     {128, 128, 8, 1, false, 0.38f, 0.55f, 0.f, 5.f},      // 128 KB, 8 waves
     // 80 KB, 4 waves.  The step: the CUs with two set the time of a round that
-    // gives the others one (gate/up of a 7B block over 203 tokens, 344 tiles,
-    // 0.92 us a slab: 64.2 us, and 53.0 as 172 of 256x128; ViT fc2 at 6144
-    // rows, 384 tiles, 0.91)
+    // gives the others one (203 x 22016, K = 4096, 344 tiles, 0.92 us a slab:
+    // as a bias product, trains over several copies of the weights, 63.8 us,
+    // and 53.6 as 172 of 256x128; inside a block under the tracer the latter,
+    // with SwiGLU, 59-62; ViT fc2 at 6144 rows, 384 tiles, 0.91)
     {128, 128, 4, 2, false, 0.54f, 0.65f, 1.0f, 5.5f, 0.12f},
     {256, 128, 8, 1, false, 0.55f, 0.89f, 0.f, 7.f},      // 144 KB
     {256, 256, 8, 1, false, 1.07f, 1.31f, 0.f, 10.f},     // 160 KB
     {256, 192, 8, 1, true, 1.05f, 1.28f, 0.f, 10.f},      // 136 KB (QKV)
     {192, 384, 8, 1, true, 1.4f, 1.8f, 0.f, 20.f},        // 144 KB (QKV)
     {192, 256, 8, 1, true, 0.9f, 1.15f, 0.f, 11.f},       // 144 KB (GELU)
-    // 120 KB.  One tile per CU where 128x128 gives half of the CUs two: 6144 x 1024, K = 4096 63.9 -> 54.3 us, 4300 x 1024
-    // 55.2 -> 42.2, 1200 x 4096 49.6 -> 45.7, 1100 x 4096, K = 11008 118 -> 102;
-    // QKV of a 7B block over 300 tokens and the connector over 1536 each about
-    // 13 us less
+    // 120 KB.  One tile per CU where 128x128 (4 waves) gives half of the CUs
+    // two.  us, weights from HBM / the same weights again: 6144 x 1024, K =
+    // 4096 60.7 -> 52.4 / 59.3 -> 52.2; 4300 x 1024 56.0 -> 44.6 / 55.2 ->
+    // 42.4; 1200 x 4096 61.1 -> 48.1 / 56.7 -> 45.8; 1100 x 4096, K = 11008
+    // 146 -> 115 / 136 -> 103
     {192, 128, 8, 1, false, 0.32f, 0.71f, 0.f, 8.5f},
 };
 // Estimated us of an M x N product over nk slabs.

@@ -179,8 +179,9 @@ hipError_t f32_to_bf16(const float* x, bf16_t* y, size_t n, hipStream_t s);
 hipError_t copy16(const void* x, void* y, size_t bytes, hipStream_t s);
 
 // ------------------------------------------------------------- fp32 debug path
-// C[M][N] (op) A[M][K] * W[N][K]^T in fp32 FMA; mode 0: C = acc + bias,
-// mode 1: C += acc + bias.
+// C[M][N] (op) A[M][K] * W[N][K]^T by fp32 MFMA, each quarter of K summed on
+// its own and the four sums added in one order whatever the tile; mode 0: C =
+// acc + bias, mode 1: C += acc + bias.
 hipError_t gemm_f32(const float* A, int lda, const float* W, int ldw, float* C, int ldc, const float* bias,
                     int mode, int M, int N, int K, hipStream_t s);
 // qkv[M][(H+2Hkv)*dh] natural order -> q/k/v/vt (fp32) with rotary on q, k.
