@@ -708,6 +708,7 @@ struct TileCost {
   bool whole_n;  // only for N a multiple of bn
   float t0, t1, t2, f;
   float step = 0.f;  // of t, as the first CU takes a second workgroup
+  float f_res = 0.f;  // of f with the residual epilogue, for each round that another follows
 };
 constexpr TileCost kTiles[T_COUNT] = {
     {64, 64, 4, 2, false, 0.25f, 0.30f, 0.44f, 2.5f},     // 64 KB of LDS
@@ -719,7 +720,12 @@ constexpr TileCost kTiles[T_COUNT] = {
     // and 53.6 as 172 of 256x128; inside a block under the tracer the latter,
     // with SwiGLU, 59-62; ViT fc2 at 6144 rows, 384 tiles, 0.91)
     {128, 128, 4, 2, false, 0.54f, 0.65f, 1.0f, 5.5f, 0.12f},
-    {256, 128, 8, 1, false, 0.55f, 0.89f, 0.f, 7.f},      // 144 KB
+    // 144 KB.  With one tile per CU the next round waits for the residual
+    // epilogue's 256 KB a tile (read and written).  us, by the fit alone and
+    // as 128x128 (4 waves), which the 2 us choose: 16384 x 8192, K = 1024 569
+    // and 438; 24576 x 1024, K = 1024 80 and 71; 4096 x 8192, K = 1024 103 and
+    // 94.  Not on the last round: 1600 x 4096, K = 4096 59 and 65.
+    {256, 128, 8, 1, false, 0.55f, 0.89f, 0.f, 7.f, 0.f, 2.f},
     {256, 256, 8, 1, false, 1.07f, 1.31f, 0.f, 10.f},     // 160 KB
     {256, 192, 8, 1, true, 1.05f, 1.28f, 0.f, 10.f},      // 136 KB (QKV)
     {192, 384, 8, 1, true, 1.4f, 1.8f, 0.f, 20.f},        // 144 KB (QKV)
@@ -732,7 +738,7 @@ constexpr TileCost kTiles[T_COUNT] = {
     {192, 128, 8, 1, false, 0.32f, 0.71f, 0.f, 8.5f},
 };
 // Estimated us of an M x N product over nk slabs.
-inline float tile_us(const TileCost& c, int M, int N, int nk) {
+inline float tile_us(const TileCost& c, int M, int N, int nk, bool residual) {
   const long w = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
   const long slots = 256L * c.per_cu, full = w / slots, rem = w % slots;
   auto round_t = [&](long x) {
@@ -741,6 +747,7 @@ inline float tile_us(const TileCost& c, int M, int N, int nk) {
   };
   float us = (float)full * (round_t(slots) * (float)nk + c.f);
   if (rem) us += round_t(rem) * (float)nk + c.f;
+  if (residual) us += c.f_res * (float)(full - (rem ? 0 : 1));
   return us;
 }
 template <class Epi>
@@ -812,7 +819,7 @@ Route choose(int M, int N, int nk) {
   float best_us = 0.f;
   for (int i = 0; i < T_COUNT; ++i) {
     if (!tile_allowed<Epi>(i) || (kTiles[i].whole_n && N % kTiles[i].bn)) continue;
-    const float us = tile_us(kTiles[i], M, N, nk);
+    const float us = tile_us(kTiles[i], M, N, nk, Epi::kDirect);
     if (r.first < 0 || us < best_us) r.first = i, best_us = us;
   }
   if constexpr (!Epi::kDirect) {
@@ -825,10 +832,10 @@ Route choose(int M, int N, int nk) {
       const long tm = (M + c.bm - 1) / c.bm, slots = 256L * c.per_cu, rounds = tm * ((N + c.bn - 1) / c.bn) / slots;
       const long cols = rounds * slots / tm * c.bn;
       if (cols <= 0 || cols >= N) continue;
-      const float first = tile_us(c, M, (int)cols, nk);
+      const float first = tile_us(c, M, (int)cols, nk, Epi::kDirect);
       for (int j = 0; j < T_COUNT; ++j) {
         if (!tile_allowed<Epi>(j) || (kTiles[j].whole_n && (N - cols) % kTiles[j].bn)) continue;
-        const float us = first + tile_us(kTiles[j], M, N - (int)cols, nk);
+        const float us = first + tile_us(kTiles[j], M, N - (int)cols, nk, Epi::kDirect);
         if (us < two_us) two_us = us, r = Route{i, (int)cols, j};
       }
     }

@@ -31,6 +31,10 @@ TILES = {RES: [T64, T64x128, T128, T128x4, T256x128, T192x128],
     (QKV, 6144, 3072, 1024, 1, [T192x384]), (RES, 6144, 1024, 1024, 1, [T128x4]),
     (GELU, 6144, 4096, 1024, 1, [T192x256]), (RES, 6144, 1024, 4096, 1, [T192x128]),
     (QKV, 4096, 1280, 896, 1, [T128x4]), (SWIGLU, 4096, 9728, 896, 1, [T256]),
+    # residual products of several rounds at short K: not the tile whose
+    # epilogue the next round waits for
+    (RES, 16384, 8192, 1024, 1, [T128x4]), (RES, 24576, 1024, 1024, 1, [T128x4]), (RES, 4096, 8192, 1024, 1, [T128x4]),
+    (RES, 1600, 4096, 4096, 1, [T256x128]),
     # test_gpu_ops, test_gpu_tiles, test_gpu_rows
     (GELU, 6144, 4096, 128, 1, [T128x4]), (GELU, 6000, 4096, 64, 1, [T128x4]), (BIAS, 2048, 16384, 64, 1, [T256]),
     (GELU, 300, 1000, 128, 1, [T64]), (BIAS, 2048, 16384, 4096, 1, [T256]), (RES, 6104, 1000, 192, 1, [T128x4]),
